@@ -11,6 +11,8 @@
 
 namespace gba {
 
+constexpr int64_t kMaxN = (int64_t(1) << 28) - 1;   // most occurrences (or request IDs) of a call
+
 // ---- token weights (Eq. 1)
 hipError_t launch_token_weights(const int64_t* tokens, int32_t K, int64_t step, int64_t iota,
                                 float* w, int64_t* staleness, int32_t* num_excluded, int32_t* err,
@@ -53,11 +55,6 @@ hipError_t launch_rows_adagrad(float* p, float* a, const float* g, const int64_t
 hipError_t launch_rows_adam(float* p, float* m, float* v, const float* g, const int64_t* rows,
                             const int32_t* active, const int64_t* num_rows, int64_t n, int32_t D,
                             int64_t R, const AdamParams& hp, int32_t* err, hipStream_t stream);
-
-// ---- device-wide exclusive scan of uint32 (in place allowed)
-size_t scan_workspace_bytes(int64_t n);
-hipError_t launch_exclusive_scan_u32(const uint32_t* in, uint32_t* out, int64_t n, uint32_t* total,
-                                     void* ws, hipStream_t stream);
 
 // ---- LSD radix sort of (u32 key, u32 occurrence index) pairs
 struct SortPlan {
@@ -139,13 +136,21 @@ size_t segments_workspace_bytes(int64_t N, int32_t D);
 bool segments_fuse_apply(int32_t D, int mode);
 hipError_t launch_segments(const SegmentArgs& a, void* ws, hipStream_t stream);
 
-// ---- runs of equal keys in sorted keys[N]: per 1024-position tile, the number
-// of runs that start before it (tile_base[ceil(N/1024)]); *total = number of runs
+// ---- runs of equal keys in sorted keys[N], N > 0: the number of runs that
+// start before each 1024-position tile, in two levels: inside the tile's group
+// of 1 << shift tiles, and per group, either each group's count (added up by
+// the consumer's blocks: run_base) or, scanned, the runs before the group.
 constexpr int64_t kRunTile = 1024;
-size_t run_heads_workspace_bytes(int64_t N);
-// n_dev (optional): the number of keys, on the device (at most N)
-hipError_t launch_run_heads(const uint32_t* keys, int64_t N, uint32_t* tile_base, uint32_t* total, void* scan_ws,
-                            hipStream_t stream, const uint32_t* n_dev = nullptr);
+constexpr int64_t kRunFoldGroups = 1024;   // most groups whose counts a consumer's blocks add up themselves
+struct RunHeads {
+  const uint32_t* tile_prefix = nullptr;   // [tiles]
+  const uint32_t* group = nullptr;         // [groups]
+  int shift = 0, groups = 0;
+  bool scanned = false;
+};
+int64_t run_groups(int64_t N);             // words of `group`
+hipError_t launch_run_heads(const uint32_t* keys, int64_t N, uint32_t* tile_prefix, uint32_t* group, RunHeads* out,
+                            hipStream_t stream);
 
 // ---- pull side: distinct IDs of a worker's request, the inverse map, the rows
 struct PullArgs {

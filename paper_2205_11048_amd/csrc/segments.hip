@@ -31,22 +31,24 @@
 #include "gba_device.hpp"
 #include "gba_internal.hpp"
 #include "optim.hpp"
+#include "run_heads.hpp"
 
 namespace gba {
 
 constexpr int kSegBlock = 256;
 constexpr int kSegWaves = kSegBlock / kWave;                 // 4
-constexpr int kRounds = 4;                                   // 16-byte loads per lane in seg_heads
+constexpr int kRounds = 4;                                   // 16-byte loads per lane and tile in run_heads
 constexpr int64_t kMetaTile = (int64_t)kSegBlock * kRounds;  // 1024 positions: 4 per thread of a block
 static_assert(kMetaTile == kRunTile, "run-head tiles are the per-position tiles");
 constexpr int kGroupSpan = 128;                              // positions per lane group (most; hot_rows)
-constexpr int kBase32Span = 32;                              // the segment count is kept every 32 positions
+constexpr int kBaseSpan = 32;                                // the segment count is kept every 32 positions (or every span)
 constexpr int kBatch = 8;                                    // positions per batch of a group
 // Row gathers in flight per group: a batch's rows are gathered and summed in
 // two parts of four, which leaves the fused row pass 121 VGPRs (4 waves per
 // SIMD) instead of 139 (3): more waves in flight beat more loads per wave.
 constexpr int kBatchPart = 4;
-constexpr int kMaxBuckets = 1024;                            // contribution lookup buckets
+constexpr int64_t kFineSpanBelow = int64_t(1) << 18;         // positions below which a lane group's span may be 16 or 8
+constexpr int kMaxBuckets = 1024;                            // contribution lookup buckets (most)
 
 // packed word of a sorted position
 constexpr uint32_t kIndexMask = (1u << 28) - 1u;  // occurrence index j (N < 2^28)
@@ -68,15 +70,30 @@ static int lanes_per_row(int D) {
 // Positions per lane group of the cold row pass: 128 for large inputs, fewer
 // below, so that a pass over a few million positions still has waves enough
 // to keep the memory busy (each group walks its span in batches, one after
-// the other).
-static int rows_span(int64_t N) { return N >= (int64_t(1) << 25) ? 128 : (N >= (int64_t(1) << 23) ? 64 : 32); }
+// the other).  Below 2^18 positions a span of 32 may leave SIMDs without a
+// wave: 16 or 8 then (20,480 positions at D = 16: 40 blocks instead of 10,
+// 13.8 us instead of 22).
+static int rows_span(int64_t N, int lpr) {
+  if (N >= (int64_t(1) << 25)) return 128;
+  if (N >= (int64_t(1) << 23)) return 64;
+  if (N >= kFineSpanBelow) return 32;
+  const int64_t waves = N * lpr / ((int64_t)kWave * 32);   // of a pass with spans of 32
+  return waves >= 2048 ? 32 : (waves >= 1024 ? 16 : 8);
+}
+// The segment count is kept at the start of every group.
+static int base_shift(int span) { return span >= 32 ? 5 : (span == 16 ? 4 : 3); }
+static_assert(kBaseSpan == 1 << 5, "base_shift");
 // positions per row-pass tile: 4 waves x (64 / LPR) groups x span positions
 static int64_t rows_tile(int lpr, int span) { return (int64_t)kSegWaves * (kWave / lpr) * span; }
 
-// Bucket width 2^q so that at most kMaxBuckets buckets cover [0, N).
-static int bucket_shift(int64_t N) {
+// Bucket width 2^q so that at most kMaxBuckets buckets cover [0, N).  Below
+// 2^18 positions, where loading the table is a good part of a block's time,
+// a few buckets per contribution (64 at least) do.
+static int bucket_shift(int64_t N, int32_t K) {
+  int64_t most = N < kFineSpanBelow ? 64 : kMaxBuckets;
+  while (most < kMaxBuckets && most < 4 * (int64_t)K) most <<= 1;
   int q = 0;
-  while (((N - 1) >> q) >= kMaxBuckets) ++q;
+  while (((N - 1) >> q) >= most) ++q;
   return q;
 }
 
@@ -97,23 +114,24 @@ constexpr int kRecipMax = 256;   // divisors with a reciprocal in the row pass's
 
 struct SegLayout {
   int64_t meta_tiles, row_tiles, hot_chunks;
-  size_t off_heads, off_total, off_scan, off_buckets, off_packed, off_base32,
-      off_cnt, off_first_acc, off_last_acc, off_fix, off_start, off_cnum, off_hot_acc, off_hot_cnt, bytes;
+  int span;              // positions per lane group of the row pass
+  size_t off_heads, off_buckets, off_packed, off_base, off_cnt, off_first_acc, off_last_acc, off_fix, off_start,
+      off_cnum, off_hot_acc, off_hot_cnt, bytes;
 };
 
 static SegLayout seg_layout(int64_t N, int32_t D) {
   SegLayout L{};
+  const int lpr = lanes_per_row(D);
+  L.span = rows_span(N, lpr);
   L.meta_tiles = N > 0 ? ceil_div(N, kMetaTile) : 1;
-  L.row_tiles = N > 0 ? ceil_div(N, rows_tile(lanes_per_row(D), rows_span(N))) : 1;
+  L.row_tiles = N > 0 ? ceil_div(N, rows_tile(lpr, L.span)) : 1;
   const size_t mt = (size_t)L.meta_tiles, rt = (size_t)L.row_tiles;
   const size_t n = (size_t)(N > 0 ? N : 1);
   size_t o = 0;
   L.off_heads = o;     o += align_up(mt * 4);
-  L.off_total = o;     o += 256;                     // head total
-  L.off_scan = o;      o += align_up(run_heads_workspace_bytes(N));
   L.off_buckets = o;   o += align_up(kMaxBuckets * 4);
   L.off_packed = o;    o += align_up((n + kGroupSpan) * 4);   // padded: whole-group vector loads stay inside
-  L.off_base32 = o;    o += align_up((n / kBase32Span + 2) * 4);
+  L.off_base = o;      o += align_up(((n >> base_shift(L.span)) + 2) * 4);
   L.off_cnt = o;       o += align_up(rt * 16);
   L.off_fix = o;       o += 256 + align_up(rt * 16);  // count, then the list
   L.off_first_acc = o; o += align_up(rt * (size_t)D * 8);
@@ -124,7 +142,10 @@ static SegLayout seg_layout(int64_t N, int32_t D) {
   // the cold positions below it
   L.off_cnum = o;      o += align_up(3 * (kHotSlots + 1) * 4);
   // per chunk of a hot run: float64 sums and (contributions, active, first and last contribution)
-  L.hot_chunks = (N > 0 ? ceil_div(N, rows_tile(lanes_per_row(D), kGroupSpan)) : 1) + kHotSlots;
+  L.hot_chunks = (N > 0 ? ceil_div(N, rows_tile(lpr, kGroupSpan)) : 1) + kHotSlots;
+  // (the run-head groups' counts lie here too: they are last read by the
+  // position pass, before the hot sums are written; hot_chunks * D * 8 is at
+  // least N / 1024 + 8192 bytes, the groups take at most N / 4096 + 4096)
   L.off_hot_acc = o;   o += align_up((size_t)L.hot_chunks * D * 8);
   L.off_hot_cnt = o;   o += align_up((size_t)L.hot_chunks * 16);
   L.bytes = o;
@@ -320,114 +341,150 @@ struct ContribTableRegs {
 static_assert(kMaxBuckets % kSegBlock == 0, "whole bucket rounds");
 
 // ------------------------------------------------------------------ kernels
-__global__ void check_offsets_kernel(const int64_t* __restrict__ off, int K, int64_t N,
-                                     int32_t* __restrict__ err) {
-  bool bad = false;
-  for (int m = threadIdx.x; m < K; m += blockDim.x) bad |= off[m] > off[m + 1];
-  if (threadIdx.x == 0) bad |= (off[0] != 0) || (off[K] != N);
-  if (bad) raise_error(err, GBA_DERR_OFFSETS);
+// What the last block of run_heads does beside the run heads for the segment
+// passes (all null / zero for a caller that needs the heads only): checks the
+// contribution offsets, builds the contribution lookup buckets and clears the
+// row pass's fixup count.
+struct HeadsPrep {
+  const int64_t* off = nullptr;   // [K + 1]
+  int32_t* bucket = nullptr;      // [nb] contribution of occurrence b << q
+  uint32_t* fix_count = nullptr;
+  int32_t* err = nullptr;
+  int64_t N = 0;                  // occurrences
+  int K = 0, q = 0, nb = 0;
+};
+
+// An offset of contribution_of's table: clamped into [0, N].
+__device__ __forceinline__ int32_t clamp_offset(int64_t o, int64_t N) {
+  return (int32_t)(o < 0 ? 0 : (o > N ? N : o));
 }
 
-// bucket[b] = contribution of occurrence b << q.
-__global__ void contrib_buckets_kernel(const int64_t* __restrict__ off, int K, int64_t N, int q,
-                                       int nb, int32_t* __restrict__ bucket) {
-  for (int b = threadIdx.x; b < nb; b += blockDim.x) {
-    const int64_t j = (int64_t)b << q;
-    int lo = 1, len = K;
-    while (len > 0) {
-      const int half = len >> 1;
-      int64_t o = off[lo + half];
-      o = o < 0 ? 0 : (o > N ? N : o);
-      if (o <= j) {
-        lo += half + 1;
-        len -= half + 1;
-      } else {
-        len = half;
-      }
-    }
-    const int m = lo - 1;
-    bucket[b] = m < K ? m : K - 1;
+__device__ __forceinline__ void heads_prep(const HeadsPrep& pr, int32_t* s_off) {
+  bool bad = false;
+  for (int m = threadIdx.x; m <= pr.K; m += (int)blockDim.x) {
+    const int64_t o = pr.off[m];
+    bad |= (m == 0 && o != 0) || (m == pr.K && o != pr.N) || (m < pr.K && o > pr.off[m + 1]);
+    s_off[m] = clamp_offset(o, pr.N);
+  }
+  if (bad) raise_error(pr.err, GBA_DERR_OFFSETS);
+  if (threadIdx.x == 0) *pr.fix_count = 0u;   // the row pass appends to the fixup list
+  __syncthreads();
+  for (int b = threadIdx.x; b < pr.nb; b += (int)blockDim.x) {
+    const int m = count_le(s_off, 1, pr.K, (uint32_t)b << pr.q) - 1;
+    pr.bucket[b] = m < pr.K ? m : pr.K - 1;
   }
 }
 
-// Run heads per 1024-position tile, one wave per tile.  Lane l holds
-// positions t0 + 4 (l + 64 c) + e (c, e < 4): each 16-byte load of the wave
-// covers 1 KB of consecutive keys, and the key before a lane's first one is
-// the last key of the lane before it.
-__global__ void __launch_bounds__(kSegBlock)
-seg_heads_kernel(const uint32_t* __restrict__ keys, int64_t N_arg, const uint32_t* __restrict__ n_dev, int64_t tiles,
-                 uint32_t* __restrict__ heads) {
-  const int lane = lane_id();
-  const int64_t tile = (int64_t)blockIdx.x * kSegWaves + threadIdx.x / kWave;
-  if (tile >= tiles) return;   // whole waves leave; no block-wide barrier follows
-  const int64_t N = n_dev ? (int64_t)*n_dev : N_arg;
-  const int64_t t0 = tile * kMetaTile;
-  if (t0 >= N) {   // past the keys on the device (a grid sized for the most keys)
-    if (lane == 0) heads[tile] = 0u;
+// Run heads: a block takes a group of WAVES consecutive 1024-position tiles,
+// one per wave, and writes the heads before each tile inside its group and
+// the group's total.  Lane l holds positions t0 + 4 (l + 64 c) + e (c, e <
+// 4): each 16-byte load of the wave covers 1 KB of consecutive keys, and the
+// key before a lane's first one is the last key of the lane before.  The last
+// block of a launch with PREP does heads_prep instead.
+template <int WAVES, bool PREP>
+__global__ void __launch_bounds__(WAVES * kWave)
+run_heads_kernel(const uint32_t* __restrict__ keys, int64_t N_arg, const uint32_t* __restrict__ n_dev, int64_t tiles,
+                 uint32_t* __restrict__ tile_prefix, uint32_t* __restrict__ group_count, HeadsPrep prep) {
+  __shared__ uint32_t s_cnt[WAVES];
+  __shared__ int32_t s_off[PREP ? GBA_MAX_K + 1 : 1];
+  if (PREP && blockIdx.x == gridDim.x - 1) {
+    heads_prep(prep, s_off);
     return;
   }
-  uint32_t carry = t0 > 0 ? keys[t0 - 1] : 0u;   // position 0 is always a head
+  const int lane = lane_id();
+  const int w = threadIdx.x / kWave;
+  const int64_t tile = (int64_t)blockIdx.x * WAVES + w;
+  const int64_t N = n_dev ? (int64_t)*n_dev : N_arg;   // the grid is sized for the most keys
+  const int64_t t0 = tile * kMetaTile;
   uint32_t cnt = 0;
+  if (t0 < N) {   // the same for the whole wave
+    uint32_t carry = t0 > 0 ? keys[t0 - 1] : 0u;   // position 0 is always a head
 #pragma unroll
-  for (int c = 0; c < kRounds; ++c) {
-    const int64_t i0 = t0 + 4 * ((int64_t)lane + (int64_t)kWave * c);
-    uint32_t k[4] = {0u, 0u, 0u, 0u};
-    if (i0 + 3 < N) {
-      const u32x4 v = *reinterpret_cast<const u32x4*>(keys + i0);
-      k[0] = v.x; k[1] = v.y; k[2] = v.z; k[3] = v.w;
-    } else {
+    for (int c = 0; c < kRounds; ++c) {
+      const int64_t i0 = t0 + 4 * ((int64_t)lane + (int64_t)kWave * c);
+      uint32_t k[4] = {0u, 0u, 0u, 0u};
+      if (i0 + 3 < N) {
+        const u32x4 v = *reinterpret_cast<const u32x4*>(keys + i0);
+        k[0] = v.x; k[1] = v.y; k[2] = v.z; k[3] = v.w;
+      } else {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) k[e] = (i0 + e < N) ? keys[i0 + e] : 0u;
+        for (int e = 0; e < 4; ++e) k[e] = (i0 + e < N) ? keys[i0 + e] : 0u;
+      }
+      uint32_t prev = __shfl_up(k[3], 1, kWave);
+      if (lane == 0) prev = carry;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int64_t p = i0 + e;
+        if (p < N) cnt += (p == 0 || k[e] != prev) ? 1u : 0u;
+        prev = k[e];
+      }
+      carry = __shfl(k[3], kWave - 1, kWave);
     }
-    uint32_t prev = __shfl_up(k[3], 1, kWave);
-    if (lane == 0) prev = carry;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int64_t p = i0 + e;
-      if (p < N) cnt += (p == 0 || k[e] != prev) ? 1u : 0u;
-      prev = k[e];
-    }
-    carry = __shfl(k[3], kWave - 1, kWave);
+    cnt = wave_sum(cnt);
   }
-  const uint32_t total = wave_sum(cnt);
-  if (lane == 0) heads[tile] = total;
+  if (lane == 0) s_cnt[w] = cnt;
+  __syncthreads();
+  if (threadIdx.x < WAVES) {
+    uint32_t before = 0;
+    for (int k = 0; k < (int)threadIdx.x; ++k) before += s_cnt[k];
+    if ((int64_t)blockIdx.x * WAVES + threadIdx.x < tiles) tile_prefix[(int64_t)blockIdx.x * WAVES + threadIdx.x] = before;
+    if (threadIdx.x == WAVES - 1) group_count[blockIdx.x] = before + s_cnt[WAVES - 1];
+  }
 }
 
-// U, the end of the last segment, and (split plan) the defaults of the hot
-// IDs' places: above every cold segment, until the position pass finds a
-// cold segment above them.
-__global__ void __launch_bounds__(kSegBlock)
-seg_finish_kernel(const SegmentArgs a, const uint32_t* __restrict__ total, uint32_t* __restrict__ seg_start,
-                  uint32_t* __restrict__ cnum, uint32_t* __restrict__ cold_below, uint32_t* __restrict__ fix_count) {
-  const uint32_t U = *total;
-  const uint32_t H = a.n_dev ? *a.hot.meta : 0u;
-  const int64_t n = a.n_dev ? (int64_t)*a.n_dev : a.N;
-  if (threadIdx.x == 0) {
-    *a.num_unique = (int64_t)U + H;
-    a.seg_offsets[U + H] = a.N;
-    seg_start[U] = (uint32_t)n;
-    *fix_count = 0u;   // the row pass appends to the fixup list
+// Exclusive scan of the group counts in place, one block: thread t owns
+// kRunScanItems consecutive groups (four 16-byte loads).
+constexpr int kRunScanBlock = 1024;
+constexpr int kRunScanItems = 16;
+__global__ void __launch_bounds__(kRunScanBlock)
+run_group_scan_kernel(uint32_t* __restrict__ group, int groups) {
+  __shared__ uint32_t tmp[kRunScanBlock / kWave + 1];
+  const int g0 = threadIdx.x * kRunScanItems;
+  uint32_t v[kRunScanItems], sum = 0;
+#pragma unroll
+  for (int k = 0; k < kRunScanItems; ++k) v[k] = g0 + k < groups ? group[g0 + k] : 0u;
+#pragma unroll
+  for (int k = 0; k < kRunScanItems; ++k) sum += v[k];
+  uint32_t total;
+  uint32_t run = block_exclusive_scan<kRunScanBlock>(sum, tmp, &total);
+#pragma unroll
+  for (int k = 0; k < kRunScanItems; ++k) {
+    if (g0 + k < groups) group[g0 + k] = run;
+    run += v[k];
   }
-  for (uint32_t h = threadIdx.x; h < H; h += kSegBlock) {
-    cnum[h] = U;
-    cold_below[h] = (uint32_t)n;
+}
+
+// No occurrences: no segments.
+__global__ void __launch_bounds__(kSegBlock)
+seg_empty_kernel(const int64_t* __restrict__ off, int K, int64_t* __restrict__ num_unique,
+                 int64_t* __restrict__ seg_offsets, int32_t* __restrict__ err) {
+  bool bad = false;
+  for (int m = threadIdx.x; m <= K; m += kSegBlock) bad |= off[m] != 0;
+  if (bad) raise_error(err, GBA_DERR_OFFSETS);
+  if (threadIdx.x == 0) {
+    *num_unique = 0;
+    seg_offsets[0] = 0;
   }
 }
 
 // Per-position pass: numbering, segment IDs and starts, packed words.
-// kMetaTilesPerBlock consecutive 1024-position tiles per block; in a tile each
-// lane takes 4 consecutive positions (16-byte loads and stores), and the
-// segment numbers come from a scan of the lanes' head counts.
-constexpr int kMetaTilesPerBlock = 4;
+// TPB consecutive 1024-position tiles per block; in a tile each lane takes 4
+// consecutive positions (16-byte loads and stores), and the segment numbers
+// come from a scan of the lanes' head counts, from the heads before the tile
+// in its group and before the group (run_base).  The lane that holds the last
+// position also writes U, the end of the last segment and the places of the
+// hot IDs above every cold key.
 constexpr int kMetaPer = 4;   // consecutive positions per lane
 static_assert(kSegBlock * kMetaPer == kMetaTile, "a block covers one tile per pass");
+template <int TPB>
 __global__ void __launch_bounds__(kSegBlock)
-seg_meta_kernel(SegmentArgs a, const uint32_t* __restrict__ tile_seg_base,
-                const int32_t* __restrict__ buckets, int q, int nbuckets, int64_t num_tiles,
-                uint32_t* __restrict__ packed, uint32_t* __restrict__ base32, uint32_t* __restrict__ seg_start,
-                uint32_t* __restrict__ cnum, uint32_t* __restrict__ cold_below) {
+seg_meta_kernel(SegmentArgs a, RunHeads heads, const int32_t* __restrict__ buckets, int q, int nbuckets,
+                int64_t num_tiles, uint32_t* __restrict__ packed, uint32_t* __restrict__ base, int bshift,
+                uint32_t* __restrict__ seg_start, uint32_t* __restrict__ cnum, uint32_t* __restrict__ cold_below) {
+  constexpr int kMetaTilesPerBlock = TPB;
   extern __shared__ int32_t s_dyn[];
   __shared__ uint32_t s_wave_heads[kSegWaves];
+  __shared__ uint32_t s_group[kSegWaves];
   // split plan: the hot IDs, their buckets and the hot occurrences below each
   __shared__ uint32_t s_hbucket[512];
   __shared__ uint32_t s_hids[kHotSlots];
@@ -444,7 +501,21 @@ seg_meta_kernel(SegmentArgs a, const uint32_t* __restrict__ tile_seg_base,
   // 512), then, when every position of the block exists, all loads of its
   // tiles, so that the tables are waited for while the tiles are in flight.
   const int64_t blk0 = (int64_t)blockIdx.x * kMetaTilesPerBlock * kMetaTile;
-  if (blk0 >= n) return;   // the grid is sized for every occurrence
+  if (blk0 >= n) {   // the grid is sized for every occurrence
+    if (n == 0 && blockIdx.x == 0) {   // every occurrence is a hot ID's
+      const uint32_t hots = *a.hot.meta;
+      for (uint32_t h = threadIdx.x; h < hots; h += kSegBlock) {
+        cnum[h] = 0u;
+        cold_below[h] = 0u;
+      }
+      if (threadIdx.x == 0) {
+        *a.num_unique = (int64_t)hots;
+        a.seg_offsets[hots] = N;
+        seg_start[0] = 0u;
+      }
+    }
+    return;
+  }
   const bool full = blk0 + kMetaTilesPerBlock * kMetaTile <= n;
   uint32_t H = 0;
   if (split) {
@@ -477,14 +548,16 @@ seg_meta_kernel(SegmentArgs a, const uint32_t* __restrict__ tile_seg_base,
       kpv[kt] = a.keys[pp];
       jpv[kt] = a.vals[pp];
       int64_t t = (int64_t)blockIdx.x * kMetaTilesPerBlock + kt;
-      sb[kt] = tile_seg_base[t < num_tiles ? t : num_tiles - 1];
+      sb[kt] = heads.tile_prefix[t < num_tiles ? t : num_tiles - 1];
     }
   }
   if (small_k)
     tables.store(a, nbuckets, s_off, s_w, s_sm, s_bucket);
   else
     load_contrib_tables(a, buckets, nbuckets, s_off, s_w, s_sm, s_bucket);
+  run_base(heads, (int64_t)blockIdx.x * kMetaTilesPerBlock, s_group);
   __syncthreads();
+  const uint32_t group_base = run_base_sum(s_group);
 
   const int w = threadIdx.x / kWave;
   const int lane = lane_id();
@@ -509,7 +582,7 @@ seg_meta_kernel(SegmentArgs a, const uint32_t* __restrict__ tile_seg_base,
       }
     }
     uint32_t word[kMetaPer];
-    uint32_t heads = 0, head_bits = 0;
+    uint32_t nheads = 0, head_bits = 0;
 #pragma unroll
     for (int e = 0; e < kMetaPer; ++e) {
       const bool valid = p0 + e < n;
@@ -528,7 +601,7 @@ seg_meta_kernel(SegmentArgs a, const uint32_t* __restrict__ tile_seg_base,
       }
       word[e] = (jv[e] & kIndexMask) | (head ? kHead : 0u) | (newc ? kNewC : 0u) |
                 (wt == 0.0f ? kZeroW : 0u) | ((wt != 0.0f && wt != 1.0f) ? kNonUnit : 0u);
-      heads += head ? 1u : 0u;
+      nheads += head ? 1u : 0u;
       head_bits |= head ? (1u << e) : 0u;
     }
     if (p0 + kMetaPer - 1 < n) {
@@ -539,13 +612,13 @@ seg_meta_kernel(SegmentArgs a, const uint32_t* __restrict__ tile_seg_base,
         if (p0 + e < n) packed[p0 + e] = word[e];
     }
     // segment numbers: the tile's base, the waves before, the lanes before
-    const uint32_t incl = wave_inclusive_scan(heads);
+    const uint32_t incl = wave_inclusive_scan(nheads);
     if (lane == kWave - 1) s_wave_heads[w] = incl;
     __syncthreads();
-    uint32_t before = seg_base + incl - heads;
+    uint32_t before = group_base + seg_base + incl - nheads;
     for (int k = 0; k < w; ++k) before += s_wave_heads[k];
     // segments that start before each group-aligned position
-    if ((p0 & (kBase32Span - 1)) == 0 && p0 < n) base32[p0 / kBase32Span] = before;
+    if ((p0 & ((int64_t(1) << bshift) - 1)) == 0 && p0 < n) base[p0 >> bshift] = before;
 #pragma unroll
     for (int e = 0; e < kMetaPer; ++e) {
       if ((head_bits >> e) & 1u) {
@@ -570,6 +643,20 @@ seg_meta_kernel(SegmentArgs a, const uint32_t* __restrict__ tile_seg_base,
         }
         ++before;
       }
+    }
+    if (p0 < n && p0 + kMetaPer >= n) {   // the last position: before = U
+      const int64_t U = before;
+      if (U + H <= N) {   // always true when the numbering is consistent
+        *a.num_unique = U + H;
+        a.seg_offsets[U + H] = N;
+        seg_start[U] = (uint32_t)n;
+      }
+      // hot IDs above every cold key
+      if (split)
+        for (uint32_t h = hot_below(a.keys[n - 1], hbucket, s_hids, H, a.hot.bshift); h < H; ++h) {
+          cnum[h] = (uint32_t)U;
+          cold_below[h] = (uint32_t)n;
+        }
     }
     __syncthreads();   // s_wave_heads is rewritten by the next tile
   };
@@ -600,21 +687,23 @@ seg_meta_kernel(SegmentArgs a, const uint32_t* __restrict__ tile_seg_base,
       kprev = a.keys[p0 - 1];
       jprev = a.vals[p0 - 1];
     }
-    tile_body(p0, key, jv, kprev, jprev, tile_seg_base[tile]);
+    tile_body(p0, key, jv, kprev, jprev, heads.tile_prefix[tile]);
   }
 }
 
 // Per-group pass: gather the kept rows and sum every run in float64.  APPLY
 // (1: Adagrad, on rows of 20 to 32 floats only) updates each finished
 // segment's row in the table as well.
-template <int LPR, int APPLY, int SPAN>
+// Each group walks `span` positions (a multiple of kBatch and of 1 << bshift).
+template <int LPR, int APPLY>
 __global__ void __launch_bounds__(kSegBlock)
-seg_rows_kernel(SegmentArgs a, const uint32_t* __restrict__ packed, const uint32_t* __restrict__ base32,
-                SegPartials part, const uint32_t* __restrict__ seg_start, const uint32_t* __restrict__ cnum) {
+seg_rows_kernel(SegmentArgs a, const uint32_t* __restrict__ packed, const uint32_t* __restrict__ base, int span,
+                int bshift, SegPartials part, const uint32_t* __restrict__ seg_start,
+                const uint32_t* __restrict__ cnum) {
   constexpr int GW = kWave / LPR;            // groups per wave
   constexpr int G = kSegWaves * GW;          // groups per block
-  constexpr int64_t TILE = (int64_t)G * SPAN;
-  static_assert(SPAN % kBatch == 0 && SPAN % kBase32Span == 0 && SPAN <= kGroupSpan, "whole batches per group");
+  const int SPAN = span;
+  const int64_t TILE = (int64_t)G * SPAN;
   // With one lane per 16 bytes of a 32-float row (eight groups of eight lanes
   // per wave), a segment that closes inside a batch is parked in LDS (its
   // row, place and counts, one slot per group and batch position) and the
@@ -674,7 +763,7 @@ seg_rows_kernel(SegmentArgs a, const uint32_t* __restrict__ packed, const uint32
     const int64_t tile = blockIdx.x;
     const int64_t p0 = tile * TILE + (int64_t)grp * SPAN;
     const int nvalid = (n - p0) >= SPAN ? SPAN : (n - p0 > 0 ? (int)(n - p0) : 0);
-    const uint32_t gbase = nvalid > 0 ? base32[p0 / kBase32Span] : 0u;
+    const uint32_t gbase = nvalid > 0 ? base[p0 >> bshift] : 0u;
     f64x4 acc = {0.0, 0.0, 0.0, 0.0};
     int cc = 0, ww = 0;
     int64_t seg = (int64_t)gbase - 1;
@@ -1312,47 +1401,71 @@ tag_update_kernel(const int64_t* __restrict__ unique_ids, const int32_t* __restr
     if (active_count[s] > 0) tag[unique_ids[s]] = step;
 }
 
-size_t run_heads_workspace_bytes(int64_t N) {
-  return scan_workspace_bytes(N > 0 ? ceil_div(N, kMetaTile) : 1);
+// Groups of 4 tiles below 4096 tiles, of 16 from there: a consumer's blocks
+// add up the counts of the groups before theirs, or, past kRunFoldGroups
+// groups, read them scanned.  A launch costs 4.5 us on a busy stream however
+// little it does; the check of the offsets, the lookup buckets, the scan of
+// the counts (one launch or three) and the segment total are six of them less
+// here (26,624-ID pull request 57 -> 50 us, 6.5 M positions 673 -> 653 us).
+static int run_group_shift(int64_t tiles) { return tiles >= 4096 ? 4 : 2; }
+
+int64_t run_groups(int64_t N) {
+  const int64_t tiles = N > 0 ? ceil_div(N, kMetaTile) : 1;
+  return ceil_div(tiles, int64_t(1) << run_group_shift(tiles));
 }
 
-hipError_t launch_run_heads(const uint32_t* keys, int64_t N, uint32_t* tile_base, uint32_t* total, void* scan_ws,
-                            hipStream_t stream, const uint32_t* n_dev) {
-  const int64_t tiles = N > 0 ? ceil_div(N, kMetaTile) : 0;
-  if (N > 0) {
-    hipLaunchKernelGGL(seg_heads_kernel, dim3((unsigned)ceil_div(tiles, kSegWaves)), dim3(kSegBlock), 0, stream,
-                       keys, N, n_dev, tiles, tile_base);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+static hipError_t launch_run_heads_prep(const uint32_t* keys, int64_t N, uint32_t* tile_prefix, uint32_t* group,
+                                        RunHeads* out, hipStream_t stream, const uint32_t* n_dev,
+                                        const HeadsPrep* prep) {
+  const int64_t tiles = ceil_div(N, kMetaTile);
+  const int64_t groups = run_groups(N);
+  out->tile_prefix = tile_prefix;
+  out->group = group;
+  out->shift = run_group_shift(tiles);
+  out->groups = (int)groups;
+  out->scanned = groups > kRunFoldGroups;
+  static_assert((kMaxN >> 10 >> 4) + 1 <= (int64_t)kRunScanBlock * kRunScanItems, "one block scans every group");
+  const dim3 grid((unsigned)(groups + (prep ? 1 : 0)));
+  const HeadsPrep pr = prep ? *prep : HeadsPrep{};
+#define GBA_RUN_HEADS(WAVES, PREP)                                                                                  \
+  hipLaunchKernelGGL((run_heads_kernel<WAVES, PREP>), grid, dim3(WAVES * kWave), 0, stream, keys, N, n_dev, tiles, \
+                     tile_prefix, group, pr)
+  if (out->shift == 4) {
+    if (prep) GBA_RUN_HEADS(16, true);
+    else GBA_RUN_HEADS(16, false);
+  } else {
+    if (prep) GBA_RUN_HEADS(4, true);
+    else GBA_RUN_HEADS(4, false);
   }
-  return launch_exclusive_scan_u32(tile_base, tile_base, tiles, total, scan_ws, stream);
+#undef GBA_RUN_HEADS
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || !out->scanned) return e;
+  hipLaunchKernelGGL(run_group_scan_kernel, dim3(1), dim3(kRunScanBlock), 0, stream, group, (int)groups);
+  return hipGetLastError();
+}
+
+hipError_t launch_run_heads(const uint32_t* keys, int64_t N, uint32_t* tile_prefix, uint32_t* group, RunHeads* out,
+                            hipStream_t stream) {
+  return launch_run_heads_prep(keys, N, tile_prefix, group, out, stream, nullptr, nullptr);
 }
 
 template <int LPR>
-static hipError_t launch_rows(const SegmentArgs& a, const uint32_t* packed, const uint32_t* base32,
+static hipError_t launch_rows(const SegmentArgs& a, const uint32_t* packed, const uint32_t* base,
                               SegPartials part, const uint32_t* seg_start, const uint32_t* cnum, HotPartials hp,
                               const int32_t* buckets, int q, int nb, const SegLayout& L, hipStream_t stream) {
   const int64_t tiles = L.row_tiles;
   const dim3 grid((unsigned)tiles), block(kSegBlock);
   if (a.ap.mode != 0 && !segments_fuse_apply(a.D, a.ap.mode)) return hipErrorInvalidValue;   // the caller applies
-  const int span = rows_span(a.N);   // the layout's tiles were sized with the same span
-#define GBA_ROWS_SPAN(AP, SP) \
-  hipLaunchKernelGGL((seg_rows_kernel<LPR, AP, SP>), grid, block, 0, stream, a, packed, base32, part, seg_start, cnum)
-#define GBA_ROWS_SPANS(AP)                 \
-  if (span == 128) GBA_ROWS_SPAN(AP, 128); \
-  else if (span == 64) GBA_ROWS_SPAN(AP, 64); \
-  else GBA_ROWS_SPAN(AP, 32);
+  const int span = L.span, bshift = base_shift(span);
+#define GBA_ROWS(AP) \
+  hipLaunchKernelGGL((seg_rows_kernel<LPR, AP>), grid, block, 0, stream, a, packed, base, span, bshift, part, seg_start, cnum)
   if constexpr (LPR == 8) {
-    if (a.ap.mode == 1) {
-      GBA_ROWS_SPANS(1)
-    } else {
-      GBA_ROWS_SPANS(0)
-    }
+    if (a.ap.mode == 1) GBA_ROWS(1);
+    else GBA_ROWS(0);
   } else {
-    GBA_ROWS_SPANS(0)
+    GBA_ROWS(0);
   }
-#undef GBA_ROWS_SPANS
-#undef GBA_ROWS_SPAN
+#undef GBA_ROWS
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   // the listed tiles (at most all of them) are spread over a fixed grid
@@ -1375,17 +1488,22 @@ static hipError_t launch_rows(const SegmentArgs& a, const uint32_t* packed, cons
   return hipSuccess;
 }
 
+// Tiles per block of the position pass: four share one load of the
+// contribution tables; below 1024 tiles one each, so that the pass has blocks
+// for every compute unit (20 tiles: 5.4 us instead of 12.4; 832 tiles: 9.3
+// instead of 14.7; 293 tiles: 7.4 instead of 15.9).
+static int meta_tiles_per_block(int64_t tiles) { return tiles >= 1024 ? 4 : 1; }
+
 bool segments_fuse_apply(int32_t D, int mode) { return mode == 1 && lanes_per_row(D) == 8; }
 
 hipError_t launch_segments(const SegmentArgs& a, void* ws, hipStream_t stream) {
   const SegLayout L = seg_layout(a.N, a.D);
   char* base = static_cast<char*>(ws);
-  uint32_t* heads = reinterpret_cast<uint32_t*>(base + L.off_heads);
-  uint32_t* total = reinterpret_cast<uint32_t*>(base + L.off_total);
-  void* scan_ws = base + L.off_scan;
+  uint32_t* tile_prefix = reinterpret_cast<uint32_t*>(base + L.off_heads);
+  uint32_t* group = reinterpret_cast<uint32_t*>(base + L.off_hot_acc);   // shared with the later hot sums
   int32_t* buckets = reinterpret_cast<int32_t*>(base + L.off_buckets);
   uint32_t* packed = reinterpret_cast<uint32_t*>(base + L.off_packed);
-  uint32_t* base32 = reinterpret_cast<uint32_t*>(base + L.off_base32);
+  uint32_t* seg_base = reinterpret_cast<uint32_t*>(base + L.off_base);
   SegPartials part;
   int32_t* cnt = reinterpret_cast<int32_t*>(base + L.off_cnt);
   part.first_cc = cnt;
@@ -1404,34 +1522,43 @@ hipError_t launch_segments(const SegmentArgs& a, void* ws, hipStream_t stream) {
   hp.cp = cnum + kHotSlots + 1;
   uint32_t* cold_below = cnum + 2 * (kHotSlots + 1);
 
-  hipLaunchKernelGGL(check_offsets_kernel, dim3(1), dim3(256), 0, stream, a.offsets, a.K, a.N, a.err);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  e = launch_run_heads(a.keys, a.N, heads, total, scan_ws, stream, a.n_dev);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(seg_finish_kernel, dim3(1), dim3(kSegBlock), 0, stream, a, (const uint32_t*)total, seg_start,
-                     cnum, cold_below, part.fix_count);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  if (a.N <= 0) return hipSuccess;
-
-  const int q = bucket_shift(a.N);
+  if (a.N <= 0) {
+    hipLaunchKernelGGL(seg_empty_kernel, dim3(1), dim3(kSegBlock), 0, stream, a.offsets, a.K, a.num_unique,
+                       a.seg_offsets, a.err);
+    return hipGetLastError();
+  }
+  const int q = bucket_shift(a.N, a.K);
   const int nb = (int)(((a.N - 1) >> q) + 1);
-  hipLaunchKernelGGL(contrib_buckets_kernel, dim3(1), dim3(256), 0, stream, a.offsets, a.K, a.N, q, nb,
-                     buckets);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
+  HeadsPrep prep;
+  prep.off = a.offsets;
+  prep.bucket = buckets;
+  prep.fix_count = part.fix_count;
+  prep.err = a.err;
+  prep.N = a.N;
+  prep.K = a.K;
+  prep.q = q;
+  prep.nb = nb;
+  RunHeads heads;
+  hipError_t e = launch_run_heads_prep(a.keys, a.N, tile_prefix, group, &heads, stream, a.n_dev, &prep);
+  if (e != hipSuccess) return e;
   const size_t lds = (size_t)(3 * a.K + 1 + nb) * sizeof(int32_t);
-  hipLaunchKernelGGL(seg_meta_kernel, dim3((unsigned)ceil_div(L.meta_tiles, kMetaTilesPerBlock)),
-                     dim3(kSegBlock), lds, stream, a, (const uint32_t*)heads, (const int32_t*)buckets, q, nb,
-                     L.meta_tiles, packed, base32, seg_start, cnum, cold_below);
+  const int tpb = meta_tiles_per_block(L.meta_tiles);
+  const dim3 mgrid((unsigned)ceil_div(L.meta_tiles, tpb));
+  if (tpb == 4)
+    hipLaunchKernelGGL(seg_meta_kernel<4>, mgrid, dim3(kSegBlock), lds, stream, a, heads, (const int32_t*)buckets, q, nb,
+                       L.meta_tiles, packed, seg_base, base_shift(L.span), seg_start, cnum, cold_below);
+  else
+    hipLaunchKernelGGL(seg_meta_kernel<1>, mgrid, dim3(kSegBlock), lds, stream, a, heads, (const int32_t*)buckets, q, nb,
+                       L.meta_tiles, packed, seg_base, base_shift(L.span), seg_start, cnum, cold_below);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   switch (lanes_per_row(a.D)) {
-    case 1: e = launch_rows<1>(a, packed, base32, part, seg_start, cnum, hp, buckets, q, nb, L, stream); break;
-    case 2: e = launch_rows<2>(a, packed, base32, part, seg_start, cnum, hp, buckets, q, nb, L, stream); break;
-    case 4: e = launch_rows<4>(a, packed, base32, part, seg_start, cnum, hp, buckets, q, nb, L, stream); break;
-    case 8: e = launch_rows<8>(a, packed, base32, part, seg_start, cnum, hp, buckets, q, nb, L, stream); break;
-    case 16: e = launch_rows<16>(a, packed, base32, part, seg_start, cnum, hp, buckets, q, nb, L, stream); break;
-    case 32: e = launch_rows<32>(a, packed, base32, part, seg_start, cnum, hp, buckets, q, nb, L, stream); break;
-    case 64: e = launch_rows<64>(a, packed, base32, part, seg_start, cnum, hp, buckets, q, nb, L, stream); break;
+    case 1: e = launch_rows<1>(a, packed, seg_base, part, seg_start, cnum, hp, buckets, q, nb, L, stream); break;
+    case 2: e = launch_rows<2>(a, packed, seg_base, part, seg_start, cnum, hp, buckets, q, nb, L, stream); break;
+    case 4: e = launch_rows<4>(a, packed, seg_base, part, seg_start, cnum, hp, buckets, q, nb, L, stream); break;
+    case 8: e = launch_rows<8>(a, packed, seg_base, part, seg_start, cnum, hp, buckets, q, nb, L, stream); break;
+    case 16: e = launch_rows<16>(a, packed, seg_base, part, seg_start, cnum, hp, buckets, q, nb, L, stream); break;
+    case 32: e = launch_rows<32>(a, packed, seg_base, part, seg_start, cnum, hp, buckets, q, nb, L, stream); break;
+    case 64: e = launch_rows<64>(a, packed, seg_base, part, seg_start, cnum, hp, buckets, q, nb, L, stream); break;
     default: return hipErrorInvalidValue;
   }
   if (e != hipSuccess) return e;

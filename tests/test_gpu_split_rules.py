@@ -1,0 +1,78 @@
+"""The edges of the rules that split the work of the segment passes: the
+positions per lane group of the row pass at small sizes, and the groups of
+1024-position tiles in which run heads are numbered (groups of 4 tiles, of 16
+from 4096 tiles, added up by every block to 1024 groups and scanned beyond)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2205_11048_amd as gba
+from compare import assert_exact
+from synth import counter
+from test_gpu_parity import _check_sparse, _run_sparse, dev, host
+import oracle
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+@pytest.mark.parametrize("D,N", [(4, 20_011), (4, 262_143), (4, 262_144), (16, 20_480), (16, 131_073),
+                                 (32, 4_099), (32, 140_001), (64, 66_001), (256, 1_025), (256, 70_003)])
+def test_row_spans_of_small_inputs(D, N):
+    """Lane groups of 8, 16 and 32 positions (and the size from which 32 is
+    always taken), with segments that end inside a group, at its end, in later
+    groups and in later tiles; dyadic rows make every sum exact."""
+    K, R = 5, 4_000
+    rng = np.random.default_rng(N)
+    ids = rng.integers(0, R, N)
+    ids[rng.random(N) < 0.25] = 1234                       # a segment over many tiles
+    ids[rng.random(N) < 0.1] = 77                          # and over many groups
+    cut = np.sort(rng.integers(0, N + 1, K - 1))
+    off = np.concatenate([[0], cut, [N]]).astype(np.int64)
+    rows = counter.values_range(N, counter.STREAM_ROWS, 0, N * D, counter.KIND_DYADIC).reshape(N, D)
+    tokens = 60 - np.array([0, 4, 1, 2, 0])
+    w, _, _ = oracle.token_weights(tokens, 60, 2)
+    res = _run_sparse(ids.astype(np.int64), rows, off, w, tokens, 60, 2, R)
+    _check_sparse(res, ids, rows, off, w, tokens, 60, 2, expect_exact=True)
+
+
+@pytest.mark.parametrize("n", [1, 1023, 1024, 1025, 4096, 4097, 16_385, 1_048_577,
+                               4096 * 1024 - 1025, 4096 * 1024 + 1, 16 * 1024 * 1024 + 1, 17 * 1024 * 1024 + 1025])
+def test_run_numbers_over_tile_groups(n):
+    """Every position's run number, across tiles, groups of tiles and the size
+    from which the group counts are scanned by a launch of their own."""
+    R, D = 3_000_000, 4
+    g = torch.Generator(device=DEV).manual_seed(n)
+    ids = torch.randint(0, R, (n,), device=DEV, generator=g)
+    table = torch.arange(R * D, device=DEV, dtype=torch.float32).reshape(R, D)
+    unique = torch.full((n,), -5, dtype=torch.int64, device=DEV)
+    inverse = torch.full((n,), -5, dtype=torch.int32, device=DEV)
+    rows = torch.empty((n, D), device=DEV)
+    num = torch.full((1,), -5, dtype=torch.int64, device=DEV)
+    err = torch.zeros(1, dtype=torch.int32, device=DEV)
+    ws = torch.empty(gba.gba_pull_workspace_size(n, R), dtype=torch.uint8, device=DEV)
+    gba.gba_pull_rows(ids, table, unique, inverse, rows, num, ws, err)
+    ref, ref_inverse = torch.unique(ids, return_inverse=True)
+    U = ref.numel()
+    assert int(err.item()) == 0 and int(num.item()) == U
+    assert torch.equal(unique[:U], ref)
+    assert torch.equal(inverse.to(torch.int64), ref_inverse)
+    assert torch.equal(rows[:U], table[ref])
+
+
+@pytest.mark.parametrize("plan", [gba.SORT_PLAIN, gba.SORT_HOT])
+@pytest.mark.parametrize("N", [1024, 4097, 1_048_575])
+def test_segments_over_tile_groups(N, plan):
+    """Segment numbers, starts and counts at the same edges, on both plans (with
+    hot IDs below, between and above the cold ones)."""
+    K, D, R = 3, 4, 50_000
+    rng = np.random.default_rng(N)
+    ids = rng.integers(5, R - 5, N)
+    for k, hot in enumerate((0, 1, 25_000, R - 2, R - 1)):
+        ids[rng.random(N) < 0.08] = hot
+    off = np.array([0, N // 3, N // 2, N], np.int64)
+    rows = counter.values_range(3, counter.STREAM_ROWS, 0, N * D, counter.KIND_DYADIC).reshape(N, D)
+    tokens = np.array([9, 8, 9])
+    w, _, _ = oracle.token_weights(tokens, 9, 3)
+    res = _run_sparse(ids.astype(np.int64), rows, off, w, tokens, 9, 3, R, plan=plan)
+    _check_sparse(res, ids, rows, off, w, tokens, 9, 3, expect_exact=True)
