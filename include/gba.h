@@ -204,20 +204,20 @@ gba_status gba_aggregate_sparse_noalloc(const int64_t* ids, const float* rows,
  * gba_apply_adam over its active rows (Alg. 2: embeddings are updated by ID
  * with the per-ID mean; Table 1 names the optimisers), in one call.  Table,
  * state and every output come out bitwise equal to those of the two separate
- * calls (the same arithmetic and the same roundings).  With
- * Adagrad on rows of 20 to 32 floats (16 < D <= 32) the optimiser runs as each
- * ID's segment is finished, so the mean never makes a round trip through
- * memory; otherwise (other widths, Adam) the call aggregates and then applies.
+ * calls (the same arithmetic and the same roundings).  The optimiser runs as
+ * each ID's segment is finished, so the mean never makes a round trip through
+ * memory.
  * ids ... num_unique   as for gba_aggregate_sparse, except that agg may be
- *                  NULL (the means are then not stored, or stored in the
- *                  workspace where they are needed).
+ *                  NULL (the means are then not stored).
  * table            [R][D] float, the embedding rows, updated in place (only
  *                  rows with W_r > 0 change).
  * accum / m, v     [R][D] float optimiser state, updated in place.
  * lr, eps, beta1, beta2, t   as for gba_apply_adagrad / gba_apply_adam.
  * workspace        at least gba_aggregate_apply_sparse_workspace_size bytes
- *                  for the optimiser (it includes room for the means where
- *                  they must go through memory and agg is NULL).
+ *                  for the optimiser where agg is NULL (for Adam, and for
+ *                  rows not of 20 to 32 floats, the size still counts room
+ *                  for the means, though the call no longer uses it), else
+ *                  gba_aggregate_sparse_workspace_size bytes.
  * table and state must be 16-byte aligned.  Errors as for
  * gba_aggregate_sparse; also GBA_ERR_NULL for a missing table or state when
  * N > 0.

@@ -194,6 +194,14 @@ gba_status gba_aggregate_sparse(const int64_t* ids, const float* rows, const int
                                    workspace_bytes, GBA_SORT_AUTO, err, stream);
 }
 
+// Room for the per-ID means that the size query of the fused calls counts for
+// Adam and for rows not of 20 to 32 floats, where those calls once put the
+// means when the caller keeps none.  The row pass now applies every row
+// itself and leaves it alone; the sizes asked for stay as callers know them.
+static size_t apply_means_bytes(int64_t N, int32_t D, int mode) {
+  return mode == GBA_OPTIMIZER_ADAGRAD && D > 16 && D <= 32 ? 0 : align_up((size_t)N * D * sizeof(float));
+}
+
 // The sparse call behind gba_aggregate_sparse(_plan) and the fused
 // aggregate-and-apply calls: ap (may be null) applies the rows as their
 // segments are finished (agg may then be null).
@@ -222,14 +230,9 @@ static gba_status sparse_call(const int64_t* ids, const float* rows, const int64
     return GBA_ERR_INVALID_ARG;
   SortPlan plan;
   const size_t need = sparse_bytes(N, D, R, sort_plan, &plan);
-  // a row apply at a width the row pass does not fuse goes through agg, in
-  // the workspace when the caller gives none
-  const bool separate = ap && !segments_fuse_apply(D, ap->mode);
-  const size_t agg_ws = (separate && !agg) ? align_up((size_t)N * D * sizeof(float)) : 0;
-  if (workspace_bytes < need + agg_ws) return GBA_ERR_WORKSPACE;
+  if (workspace_bytes < need + ((ap && !agg) ? apply_means_bytes(N, D, ap->mode) : 0)) return GBA_ERR_WORKSPACE;
 
   char* ws = static_cast<char*>(workspace);
-  float* g = agg ? agg : (agg_ws ? reinterpret_cast<float*>(ws + need) : nullptr);
   const uint32_t* keys = nullptr;
   const uint32_t* vals = nullptr;
   // with the hot-key plan the frequent IDs are reduced apart from the rest
@@ -261,20 +264,11 @@ static gba_status sparse_call(const int64_t* ids, const float* rows, const int64
   a.seg_offsets = seg_offsets;
   a.contrib_count = contrib_count;
   a.active_count = active_count;
-  a.agg = g;
+  a.agg = agg;
   a.num_unique = num_unique;
   a.err = err;
-  if (ap && !separate) a.ap = *ap;
-  e = launch_segments(a, ws + align_up(plan.bytes), stream);
-  if (e != hipSuccess || !separate || N == 0) return from_hip(e);
-  // the rows apply after the aggregation, over the active distinct IDs
-  if (ap->mode == 2)
-    e = launch_rows_adam(ap->p, ap->s1, ap->s2, g, unique_ids, active_count, num_unique, N, D, R,
-                         AdamParams{ap->lr, ap->beta1, ap->beta2, ap->eps, ap->bc1, ap->bc2}, err, stream);
-  else
-    e = launch_rows_adagrad(ap->p, ap->s1, g, unique_ids, active_count, num_unique, N, D, R, ap->lr, ap->eps, err,
-                            stream);
-  return from_hip(e);
+  if (ap) a.ap = *ap;
+  return from_hip(launch_segments(a, ws + align_up(plan.bytes), stream));
 }
 
 gba_status gba_aggregate_sparse_plan(const int64_t* ids, const float* rows, const int64_t* contrib_offsets,
@@ -313,7 +307,7 @@ gba_status gba_aggregate_apply_sparse_workspace_size(int64_t N, int32_t K, int32
                                                      size_t* bytes) {
   if (optimizer != GBA_OPTIMIZER_ADAGRAD && optimizer != GBA_OPTIMIZER_ADAM) return GBA_ERR_INVALID_ARG;
   const gba_status st = gba_aggregate_sparse_workspace_size(N, K, D, R, bytes);
-  if (st == GBA_OK && !segments_fuse_apply(D, optimizer)) *bytes += align_up((size_t)N * D * sizeof(float));
+  if (st == GBA_OK) *bytes += apply_means_bytes(N, D, optimizer);
   return st;
 }
 
@@ -331,8 +325,7 @@ gba_status gba_aggregate_apply_sparse_adagrad(const int64_t* ids, const float* r
   ap.mode = GBA_OPTIMIZER_ADAGRAD;
   ap.p = table;
   ap.s1 = accum;
-  ap.lr = lr;
-  ap.eps = eps;
+  ap.c = opt_f32(lr, eps);
   return sparse_call(ids, rows, contrib_offsets, K, N, D, R, w, tokens, step, iota, tag, decay, norm, unique_ids,
                      seg_offsets, contrib_count, active_count, agg, num_unique, workspace, workspace_bytes,
                      GBA_SORT_AUTO, &ap, err, stream);
@@ -355,12 +348,7 @@ gba_status gba_aggregate_apply_sparse_adam(const int64_t* ids, const float* rows
   ap.p = table;
   ap.s1 = m;
   ap.s2 = v;
-  ap.lr = hp.lr;
-  ap.eps = hp.eps;
-  ap.beta1 = hp.beta1;
-  ap.beta2 = hp.beta2;
-  ap.bc1 = hp.bc1;
-  ap.bc2 = hp.bc2;
+  ap.c = opt_f32(hp.lr, hp.eps, hp.beta1, hp.beta2, hp.bc1, hp.bc2);
   return sparse_call(ids, rows, contrib_offsets, K, N, D, R, w, tokens, step, iota, tag, decay, norm, unique_ids,
                      seg_offsets, contrib_count, active_count, agg, num_unique, workspace, workspace_bytes,
                      GBA_SORT_AUTO, &ap, err, stream);

@@ -8,6 +8,7 @@
 #include <stdint.h>
 
 #include "gba.h"
+#include "optim.hpp"
 
 namespace gba {
 
@@ -100,7 +101,7 @@ struct RowApply {
   float* p = nullptr;    // [R][D] table
   float* s1 = nullptr;   // [R][D] Adagrad accumulator or Adam m
   float* s2 = nullptr;   // [R][D] Adam v
-  double lr = 0.0, eps = 0.0, beta1 = 0.0, beta2 = 0.0, bc1 = 1.0, bc2 = 1.0;
+  OptF32 c{};            // the update's constants
 };
 
 struct SegmentArgs {
@@ -129,11 +130,6 @@ struct SegmentArgs {
   RowApply ap;            // mode 0: agg is written and no row is applied
 };
 size_t segments_workspace_bytes(int64_t N, int32_t D);
-// Whether launch_segments applies the rows itself for this optimiser (ap.mode)
-// at width D: Adagrad on rows of 20 to 32 floats, where it was measured
-// faster than the aggregation followed by the separate row apply (Adam, with
-// two state rows per update, was measured slower fused).
-bool segments_fuse_apply(int32_t D, int mode);
 hipError_t launch_segments(const SegmentArgs& a, void* ws, hipStream_t stream);
 
 // ---- runs of equal keys in sorted keys[N], N > 0: the number of runs that

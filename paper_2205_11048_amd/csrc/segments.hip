@@ -227,32 +227,41 @@ __device__ __forceinline__ int contribution_global(const int64_t* off, int K, ui
   return m < 0 ? 0 : (m < K ? m : K - 1);
 }
 
-// Adagrad on one lane's 4 floats of a row, with the row apply's arithmetic.  The fused row pass applies
-// Adagrad only (segments_fuse_apply); Adam goes through the separate apply.
-__device__ __forceinline__ void adagrad4(const RowApply& ap, f32x4& pv, f32x4& s1, f32x4 g) {
-  float pe[4] = {pv.x, pv.y, pv.z, pv.w}, ae[4] = {s1.x, s1.y, s1.z, s1.w};
+// The optimiser on one lane's 4 floats of a row (mode 1 Adagrad, 2 Adam), with
+// the row apply's arithmetic.
+__device__ __forceinline__ void update4(int mode, const OptF32& c, f32x4& pv, f32x4& s1, f32x4& s2, f32x4 g) {
+  float pe[4] = {pv.x, pv.y, pv.z, pv.w}, ae[4] = {s1.x, s1.y, s1.z, s1.w}, ve[4] = {s2.x, s2.y, s2.z, s2.w};
   const float ge[4] = {g.x, g.y, g.z, g.w};
-  const OptF32 c = opt_f32(ap.lr, ap.eps);
+  if (mode == 2) {
 #pragma unroll
-  for (int e = 0; e < 4; ++e) adagrad_update_f32(pe[e], ae[e], ge[e], c);
+    for (int e = 0; e < 4; ++e) adam_update_f32(pe[e], ae[e], ve[e], ge[e], c);
+    s2 = f32x4{ve[0], ve[1], ve[2], ve[3]};
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) adagrad_update_f32(pe[e], ae[e], ge[e], c);
+  }
   pv = f32x4{pe[0], pe[1], pe[2], pe[3]};
   s1 = f32x4{ae[0], ae[1], ae[2], ae[3]};
 }
 
-// Row r updated with mean g (one lane's 16 bytes): load, Adagrad, store.
-__device__ __forceinline__ void apply_row_part(const RowApply& ap, int64_t r, int D, int lane, f32x4 g) {
+// Row r updated with mean g (one lane's 16 bytes): load, update, store.
+__device__ __forceinline__ void apply_row_part(const RowApply& ap, int mode, int64_t r, int D, int lane, f32x4 g) {
   const int64_t at = r * D + lane * 4;
   f32x4 pv = load_stream(reinterpret_cast<const f32x4*>(ap.p + at));
   f32x4 s1 = load_stream(reinterpret_cast<const f32x4*>(ap.s1 + at));
-  adagrad4(ap, pv, s1, g);
+  f32x4 s2 = mode == 2 ? load_stream(reinterpret_cast<const f32x4*>(ap.s2 + at)) : f32x4{0.f, 0.f, 0.f, 0.f};
+  update4(mode, ap.c, pv, s1, s2, g);
   store_stream(reinterpret_cast<f32x4*>(ap.p + at), pv);
   store_stream(reinterpret_cast<f32x4*>(ap.s1 + at), s1);
+  if (mode == 2) store_stream(reinterpret_cast<f32x4*>(ap.s2 + at), s2);
 }
 
 // out: the segment's place among all distinct IDs.  The mean goes to agg
-// (when given) and, with the fused Adagrad apply (mode 1; a constant in the row pass),
-// into the optimiser update of row `row`, or where row < 0 of the ID the
-// position pass wrote for this place (written by an earlier launch).
+// (when given) and, with a fused apply (mode 1 Adagrad, 2 Adam; a constant in
+// the row pass), into the optimiser update of row `row`, or where row < 0 of
+// the ID the position pass wrote for this place (written by an earlier
+// launch); that row's tag then carries the step (per-ID decay: every tag of
+// this call was read by an earlier launch, or is the hot ID's own).
 __device__ __forceinline__ void finalize_segment(const SegmentArgs& a, int64_t seg, f64x4 acc,
                                                  int cc, int ww, int lane, bool lane_on, int mode,
                                                  int64_t row = -1) {
@@ -263,7 +272,10 @@ __device__ __forceinline__ void finalize_segment(const SegmentArgs& a, int64_t s
     store_stream(reinterpret_cast<f32x4*>(a.agg + seg * (int64_t)a.D + lane * 4), g);   // read once, by the apply
   if (mode != 0 && lane_on && ww > 0) {
     const int64_t r = row >= 0 ? row : a.unique_ids[seg];
-    if (r >= 0 && r < a.R) apply_row_part(a.ap, r, a.D, lane, g);   // always in range when the numbering is consistent
+    if (r >= 0 && r < a.R) {   // always in range when the numbering is consistent
+      apply_row_part(a.ap, mode, r, a.D, lane, g);
+      if (a.decay == GBA_DECAY_ID_TAG && lane == 0) a.tag[r] = (int32_t)a.step;
+    }
   }
   if (lane == 0) {
     a.contrib_count[seg] = cc;
@@ -692,9 +704,23 @@ seg_meta_kernel(SegmentArgs a, RunHeads heads, const int32_t* __restrict__ bucke
 }
 
 // Per-group pass: gather the kept rows and sum every run in float64.  APPLY
-// (1: Adagrad, on rows of 20 to 32 floats only) updates each finished
-// segment's row in the table as well.
+// (1 Adagrad, 2 Adam) updates each finished segment's row in the table as well.
 // Each group walks `span` positions (a multiple of kBatch and of 1 << bshift).
+//
+// A segment that closes is parked in LDS: its mean, place, counts and (with a
+// row apply) row go to the next free entry of the wave's ring, numbered by a
+// ballot of the closing groups.  When kPop entries wait, the wave writes them
+// together, GW rows per store with every lane busy and the table and state
+// rows of kR such rounds requested before the first is used; otherwise each
+// group would store and update as its segments close while the lanes of the
+// other groups idle.  Wide rows that are only stored (two groups per wave or
+// one) are written as they close (D = 128, 300,007 positions: 71 us, parked
+// 100).  Bound: random row accesses, some 35-39 G 128-byte lines a second
+// read and written at every width (a read-only gather reaches 47-50); D = 32
+// with Adam, 6.5 M positions, per-ID decay: 303 us for this pass against 144 +
+// 183 + 22 for the pass, the row apply and the tags as launches of their own;
+// D = 16 with Adam 219 against 104 + 119, D = 64 with Adagrad 137 against 63 +
+// 74 (both storing the means too), so every width applies its rows here.
 template <int LPR, int APPLY>
 __global__ void __launch_bounds__(kSegBlock)
 seg_rows_kernel(SegmentArgs a, const uint32_t* __restrict__ packed, const uint32_t* __restrict__ base, int span,
@@ -704,35 +730,24 @@ seg_rows_kernel(SegmentArgs a, const uint32_t* __restrict__ packed, const uint32
   constexpr int G = kSegWaves * GW;          // groups per block
   const int SPAN = span;
   const int64_t TILE = (int64_t)G * SPAN;
-  // With one lane per 16 bytes of a 32-float row (eight groups of eight lanes
-  // per wave), a segment that closes inside a batch is parked in LDS (its
-  // row, place and counts, one slot per group and batch position) and the
-  // wave writes the batch's parked segments together afterwards, eight rows
-  // per store with every lane busy, instead of each group storing as its
-  // segments close while the other groups' lanes idle.
-  // With a row apply the parked segment also keeps its row (its ID), and the
-  // wave updates the batch's rows together: the table and state rows of
-  // several rounds of parked segments are requested before the first is used.
-  constexpr bool kPark = LPR == 8 && GW == kBatch;
-  static_assert(APPLY == 0 || kPark, "the row apply is fused where segments are parked");
-  static_assert(APPLY == 0 || APPLY == 1, "the fused row apply is Adagrad only");
-  constexpr int kSlots = GW * kBatch;
+  static_assert(APPLY >= 0 && APPLY <= 2, "none, Adagrad, Adam");
   // rows gathered at a time: the batch in parts of kPart (registers: each
   // lane holds kPart 16-byte row pieces while they are in flight)
   constexpr int kPart = kBatchPart;
-  __shared__ f32x4 s_park[kPark ? kSegWaves : 1][kPark ? kSlots : 1][LPR];
-  __shared__ uint32_t s_park_out[kPark ? kSegWaves : 1][kSlots];
-  __shared__ uint32_t s_park_cw[kPark ? kSegWaves : 1][kSlots];
-  __shared__ uint32_t s_park_list[kPark ? kSegWaves : 1][kSlots];
+  constexpr bool kPark = APPLY != 0 || LPR <= 16;
+  constexpr int kR = LPR <= 2 ? 1 : ((APPLY == 1 && LPR >= 8) ? 4 : 2);   // rounds of rows in flight (registers)
+  constexpr int kPop = kR * GW;
+  // a part adds at most kPart * GW entries to fewer than kPop
+  constexpr int kSlots = kPark ? kPop + kPart * GW : kWave * (int)sizeof(f64x4) / (LPR * (int)sizeof(f32x4));
+  auto ring = [](int x) { return x < kSlots ? x : x - kSlots; };   // x < 2 kSlots
+  __shared__ f32x4 s_park[kSegWaves][kSlots][LPR];
+  __shared__ uint32_t s_park_out[kPark ? kSegWaves : 1][kPark ? kSlots : 1];
+  __shared__ uint32_t s_park_cw[kPark ? kSegWaves : 1][kPark ? kSlots : 1];
   __shared__ uint32_t s_park_key[APPLY ? kSegWaves : 1][APPLY ? kSlots : 1];
   // per-lane chain sums at the end of the groups: in the parking area of the
-  // lane's own wave when parking (free by then), else their own array
-  static_assert(!kPark || sizeof(s_park[0]) >= kWave * sizeof(f64x4), "chain sums fit a wave's parking area");
-  __shared__ f64x4 s_acc_own[kPark ? 1 : kSegBlock];
-  auto s_acc_at = [&](int t) -> f64x4& {
-    if (kPark) return reinterpret_cast<f64x4*>(&s_park[t / kWave][0][0])[t % kWave];
-    return s_acc_own[t];
-  };
+  // lane's own wave, free by then
+  static_assert(sizeof(s_park[0]) >= kWave * sizeof(f64x4), "chain sums fit a wave's parking area");
+  auto s_acc_at = [&](int t) -> f64x4& { return reinterpret_cast<f64x4*>(&s_park[t / kWave][0][0])[t % kWave]; };
   __shared__ int32_t s_cc[G], s_ww[G];
   __shared__ uint32_t s_seg[G], s_flags[G];
   __shared__ uint32_t s_cnum[kHotSlots];
@@ -777,7 +792,7 @@ seg_rows_kernel(SegmentArgs a, const uint32_t* __restrict__ packed, const uint32
     f64x4 facc = {0.0, 0.0, 0.0, 0.0};
     int fcc = 0, fww = 0;
     bool owner = false;
-    uint32_t parked = 0;   // batch positions at which a segment of this group was parked
+    int parked = 0, first_parked = 0;   // entries of the wave's ring, and its first (the same in every lane)
     uint32_t cur_key = (APPLY && nvalid > 0) ? a.keys[p0] : 0u;   // row of the open segment (row apply)
     // Words of the batch at i0 (the packed array is padded by a group span, so
     // whole vectors stay in bounds past the group's end).
@@ -834,25 +849,40 @@ seg_rows_kernel(SegmentArgs a, const uint32_t* __restrict__ packed, const uint32
         // keep each row's float64 widening next to its use: hoisting all of
         // them costs registers and the waves that keep gathers in flight
         __builtin_amdgcn_sched_barrier(0);
+        // groups whose open segment ends before this position, apart from one that began before the group
+        const bool head = i < nvalid && (word[u] & kHead);
+        const bool closes = head && i > 0 && !(in_first && first_open);
+        const uint64_t mc = kPark ? __ballot(closes) : 0ull;
         if (i < nvalid) {
-          if (word[u] & kHead) {
+          if (head) {
             if (i > 0) {
-              if (in_first && first_open) {
+              if (!closes) {
                 facc = acc; fcc = cc; fww = ww; owner = true;
-              } else if (kPark) {
-                const int slot = (lane / LPR) * kBatch + u;
+              } else {
                 const double div = by_k ? (double)a.K : (double)cc;
                 // a segment has at most K contributions: the table covers every count when K is small
                 const double y = by_k ? recip_k : (small_k ? s_recip[cc] : 1.0 / div);
-                if (lane_on) s_park[w][slot][gl] = narrow(div_rounded(acc, div, y));
-                if (gl == 0) {
-                  s_park_out[w][slot] = (uint32_t)(seg + hb);
-                  s_park_cw[w][slot] = (uint32_t)cc | ((uint32_t)ww << 16);
-                  if (APPLY) s_park_key[w][slot] = cur_key;
+                const f32x4 g = narrow(div_rounded(acc, div, y));
+                if (kPark) {
+                  const uint32_t below =
+                      __builtin_amdgcn_mbcnt_hi((uint32_t)(mc >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mc, 0u));
+                  const int slot = ring(ring(first_parked + parked) + (int)(below / LPR));
+                  if (lane_on) s_park[w][slot][gl] = g;
+                  if (gl == 0) {
+                    s_park_out[w][slot] = (uint32_t)(seg + hb);
+                    s_park_cw[w][slot] = (uint32_t)cc | ((uint32_t)ww << 16);
+                    if (APPLY) s_park_key[w][slot] = cur_key;
+                  }
+                } else {
+                  const int64_t out = seg + hb;
+                  if (out < N) {   // always true when the numbering is consistent
+                    if (lane_on) store_stream(reinterpret_cast<f32x4*>(a.agg + out * D + gl * 4), g);
+                    if (gl == 0) {
+                      a.contrib_count[out] = cc;
+                      a.active_count[out] = ww;
+                    }
+                  }
                 }
-                parked |= 1u << u;
-              } else {
-                finalize_segment(a, seg + hb, acc, cc, ww, gl, lane_on, APPLY);
               }
               in_first = false;
             }
@@ -878,85 +908,64 @@ seg_rows_kernel(SegmentArgs a, const uint32_t* __restrict__ packed, const uint32
           cc += nc;
           ww += (nc && !zero) ? 1 : 0;
         }
+        parked += __popcll(mc) / LPR;
       }
     };
-    // The parked segments of a batch, written by the whole wave: lane L
-    // stands for slot L (group L / 8, batch position L % 8).
-    auto flush = [&]() {
-      const bool mine = (parked >> gl) & 1u;
-      const uint64_t m = __ballot(mine);
-      if (mine) s_park_list[w][__popcll(m & lanemask_lt())] = (uint32_t)lane;
+    // The first `count` (at most kPop) parked segments, written by the whole
+    // wave: the group of lane / LPR takes entries lane / LPR + GW r.
+    auto pop = [&](int count) {
       __builtin_amdgcn_wave_barrier();
-      const int E = __popcll(m);
-      if (APPLY) {
-        // kR rounds at a time: the table and state rows of all their active
-        // segments are requested, then updated (a lane without one reads the
-        // table's first 16 bytes and writes nothing)
-        constexpr int kR = 4;
-        for (int b = 0; b < E; b += kR * GW) {
-          f32x4 pv[kR], sv[kR];
-          uint32_t slot[kR];
-          int64_t outv[kR], row[kR];
-          bool act[kR];
+      f32x4 pv[kR], sv[kR], vv[kR];
+      int slot[kR];
+      int64_t outv[kR], row[kR];
+      bool act[kR];
 #pragma unroll
-          for (int r = 0; r < kR; ++r) {
-            const int e = b + r * GW + lane / LPR;
-            slot[r] = e < E ? s_park_list[w][e] : 0u;
-            outv[r] = e < E ? (int64_t)s_park_out[w][slot[r]] : N;   // out < N when the numbering is consistent
-            act[r] = outv[r] < N && (s_park_cw[w][slot[r]] >> 16) > 0 && lane_on &&
-                     (int64_t)s_park_key[w][slot[r]] < a.R;   // sorted keys are below R
-            row[r] = act[r] ? (int64_t)s_park_key[w][slot[r]] : 0;
-            const int64_t at = act[r] ? row[r] * D + gl * 4 : 0;   // inactive lanes read the table's first 16 bytes
-            pv[r] = load_stream(reinterpret_cast<const f32x4*>(a.ap.p + at));
-            sv[r] = load_stream(reinterpret_cast<const f32x4*>(a.ap.s1 + at));
-          }
-#pragma unroll
-          for (int r = 0; r < kR; ++r) {
-            if (outv[r] >= N) continue;
-            const f32x4 g = s_park[w][slot[r]][gl];
-            if (lane_on && a.agg) store_stream(reinterpret_cast<f32x4*>(a.agg + outv[r] * D + gl * 4), g);
-            if (gl == 0) {
-              const uint32_t v = s_park_cw[w][slot[r]];
-              a.contrib_count[outv[r]] = (int32_t)(v & 0xffffu);
-              a.active_count[outv[r]] = (int32_t)(v >> 16);
-            }
-            if (act[r]) {
-              const int64_t at = row[r] * D + gl * 4;
-              adagrad4(a.ap, pv[r], sv[r], g);
-              store_stream(reinterpret_cast<f32x4*>(a.ap.p + at), pv[r]);
-              store_stream(reinterpret_cast<f32x4*>(a.ap.s1 + at), sv[r]);
-            }
-          }
-        }
-      } else {
-        for (int b = 0; b < E; b += GW) {
-          const int e = b + lane / LPR;
-          if (e < E) {
-            const uint32_t slot = s_park_list[w][e];
-            const int64_t out = s_park_out[w][slot];
-            if (out < N) {   // always true when the numbering is consistent
-              if (lane_on) store_stream(reinterpret_cast<f32x4*>(a.agg + out * D + gl * 4), s_park[w][slot][gl]);
-              if (gl == 0) {
-                const uint32_t v = s_park_cw[w][slot];
-                a.contrib_count[out] = (int32_t)(v & 0xffffu);
-                a.active_count[out] = (int32_t)(v >> 16);
-              }
-            }
-          }
+      for (int r = 0; r < kR; ++r) {
+        const int e = r * GW + lane / LPR;
+        slot[r] = ring(first_parked + e);
+        outv[r] = e < count ? (int64_t)s_park_out[w][slot[r]] : N;   // out < N when the numbering is consistent
+        if (APPLY) {
+          // sorted keys are below R; a lane without a row reads the table's first 16 bytes and writes nothing
+          const uint32_t k = s_park_key[w][slot[r]];
+          act[r] = outv[r] < N && (s_park_cw[w][slot[r]] >> 16) > 0 && lane_on && (int64_t)k < a.R;
+          row[r] = act[r] ? (int64_t)k : 0;
+          const int64_t at = act[r] ? row[r] * D + gl * 4 : 0;
+          pv[r] = load_stream(reinterpret_cast<const f32x4*>(a.ap.p + at));
+          sv[r] = load_stream(reinterpret_cast<const f32x4*>(a.ap.s1 + at));
+          if (APPLY == 2) vv[r] = load_stream(reinterpret_cast<const f32x4*>(a.ap.s2 + at));
         }
       }
-      __builtin_amdgcn_wave_barrier();   // the next batch reuses the slots
-      parked = 0;
+#pragma unroll
+      for (int r = 0; r < kR; ++r) {
+        if (outv[r] >= N) continue;
+        const f32x4 g = s_park[w][slot[r]][gl];
+        if (lane_on && (!APPLY || a.agg)) store_stream(reinterpret_cast<f32x4*>(a.agg + outv[r] * D + gl * 4), g);
+        if (gl == 0) {
+          const uint32_t v = s_park_cw[w][slot[r]];
+          a.contrib_count[outv[r]] = (int32_t)(v & 0xffffu);
+          a.active_count[outv[r]] = (int32_t)(v >> 16);
+          // the tags of this call were read by the position pass
+          if (APPLY && a.decay == GBA_DECAY_ID_TAG && act[r]) a.tag[row[r]] = (int32_t)a.step;
+        }
+        if (APPLY && act[r]) {
+          const int64_t at = row[r] * D + gl * 4;
+          update4(APPLY, a.ap.c, pv[r], sv[r], vv[r], g);
+          store_stream(reinterpret_cast<f32x4*>(a.ap.p + at), pv[r]);
+          store_stream(reinterpret_cast<f32x4*>(a.ap.s1 + at), sv[r]);
+          if (APPLY == 2) store_stream(reinterpret_cast<f32x4*>(a.ap.s2 + at), vv[r]);
+        }
+      }
+      first_parked = ring(first_parked + count);
+      parked -= count;
+      __builtin_amdgcn_wave_barrier();   // the entries are reused from here
     };
-    // every group of a wave runs the wave's longest group's batches, so the
-    // flush sees the whole wave
+    // every group of a wave runs the wave's longest group's batches, so that
+    // the whole wave takes part in every ballot and pop
     int iters = nvalid;
-    if (kPark) {
 #pragma unroll
-      for (int off = kWave / 2; off > 0; off >>= 1) {
-        const int o = __shfl_xor(iters, off, kWave);
-        iters = o > iters ? o : iters;
-      }
+    for (int off = kWave / 2; off > 0; off >>= 1) {
+      const int o = __shfl_xor(iters, off, kWave);
+      iters = o > iters ? o : iters;
     }
     for (int i0 = 0; i0 < iters; i0 += kBatch) {
       uint32_t word[kBatch], kk[kBatch];
@@ -976,9 +985,13 @@ seg_rows_kernel(SegmentArgs a, const uint32_t* __restrict__ packed, const uint32
         f32x4 rv[kPart];
         gather(i0, u0, word, rv, use);
         sum_batch(i0, u0, word, kk, rv, use, weighted);
+        if (kPark)
+          while (parked >= kPop) pop(kPop);
       }
-      if (kPark) flush();
     }
+
+    if (kPark)
+      while (parked > 0) pop(parked < kPop ? parked : kPop);
 
     bool last_open = false, pass = false;
     if (nvalid > 0) {
@@ -1455,16 +1468,12 @@ static hipError_t launch_rows(const SegmentArgs& a, const uint32_t* packed, cons
                               const int32_t* buckets, int q, int nb, const SegLayout& L, hipStream_t stream) {
   const int64_t tiles = L.row_tiles;
   const dim3 grid((unsigned)tiles), block(kSegBlock);
-  if (a.ap.mode != 0 && !segments_fuse_apply(a.D, a.ap.mode)) return hipErrorInvalidValue;   // the caller applies
   const int span = L.span, bshift = base_shift(span);
 #define GBA_ROWS(AP) \
   hipLaunchKernelGGL((seg_rows_kernel<LPR, AP>), grid, block, 0, stream, a, packed, base, span, bshift, part, seg_start, cnum)
-  if constexpr (LPR == 8) {
-    if (a.ap.mode == 1) GBA_ROWS(1);
-    else GBA_ROWS(0);
-  } else {
-    GBA_ROWS(0);
-  }
+  if (a.ap.mode == 1) GBA_ROWS(1);
+  else if (a.ap.mode == 2) GBA_ROWS(2);
+  else GBA_ROWS(0);
 #undef GBA_ROWS
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -1493,8 +1502,6 @@ static hipError_t launch_rows(const SegmentArgs& a, const uint32_t* packed, cons
 // for every compute unit (20 tiles: 5.4 us instead of 12.4; 832 tiles: 9.3
 // instead of 14.7; 293 tiles: 7.4 instead of 15.9).
 static int meta_tiles_per_block(int64_t tiles) { return tiles >= 1024 ? 4 : 1; }
-
-bool segments_fuse_apply(int32_t D, int mode) { return mode == 1 && lanes_per_row(D) == 8; }
 
 hipError_t launch_segments(const SegmentArgs& a, void* ws, hipStream_t stream) {
   const SegLayout L = seg_layout(a.N, a.D);
@@ -1562,7 +1569,7 @@ hipError_t launch_segments(const SegmentArgs& a, void* ws, hipStream_t stream) {
     default: return hipErrorInvalidValue;
   }
   if (e != hipSuccess) return e;
-  if (a.decay == GBA_DECAY_ID_TAG) {
+  if (a.decay == GBA_DECAY_ID_TAG && a.ap.mode == 0) {   // a fused apply writes the tags as it goes
     int64_t blocks = ceil_div(a.N, kSegBlock);
     if (blocks > 4096) blocks = 4096;
     hipLaunchKernelGGL(tag_update_kernel, dim3((unsigned)blocks), dim3(kSegBlock), 0, stream,

@@ -39,8 +39,8 @@ class GBAStep:
         self.agg = torch.empty((cap, D), dtype=torch.float32, device=dev)
         self.num_unique = torch.zeros(1, dtype=torch.int64, device=dev)
         ws = gba_aggregate_sparse_workspace_size(N, K, D, R)
-        # the fused sparse call needs no more workspace where it applies the
-        # rows as it goes; otherwise the means go through agg (ours)
+        # where the fused sparse call's size query counts room for the means,
+        # the call is given agg (ours) and stores them there
         self.fuses_rows = {opt: gba_aggregate_apply_sparse_workspace_size(N, K, D, R, opt) == ws
                            for opt in ("adagrad", "adam")}
         self.workspace = torch.empty(ws, dtype=torch.uint8, device=dev)

@@ -9,7 +9,8 @@ import torch
 import paper_2205_11048_amd as gba
 from compare import assert_exact
 from synth import counter
-from test_gpu_parity import _check_sparse, _run_sparse, dev, host
+from synth import workload
+from test_gpu_parity import _check_sparse, _run_sparse, _sparse_step, _table_and_state, dev
 import oracle
 
 pytestmark = pytest.mark.gpu
@@ -76,3 +77,37 @@ def test_segments_over_tile_groups(N, plan):
     w, _, _ = oracle.token_weights(tokens, 9, 3)
     res = _run_sparse(ids.astype(np.int64), rows, off, w, tokens, 9, 3, R, plan=plan)
     _check_sparse(res, ids, rows, off, w, tokens, 9, 3, expect_exact=True)
+
+
+@pytest.mark.parametrize("opt,decay", [("adagrad", "token"), ("adagrad", "id_tag"), ("adam", "id_tag")])
+@pytest.mark.parametrize("D", [4, 12, 128, 256])
+def test_fused_apply_at_the_other_widths(D, opt, decay):
+    """The row pass applies the rows at every number of lanes per row (one to
+    64 groups per wave share a ring of finished segments): table, state, tags and
+    counts are bitwise those of the aggregation and the row apply as two calls.
+    Few long segments and many short ones, so that the ring fills unevenly."""
+    K, R = 9, 30_000
+    rng = np.random.default_rng(D)
+    sizes = rng.integers(0, 5_000, K)
+    N = int(sizes.sum())
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    ids = np.where(rng.random(N) < 0.3, rng.integers(0, 3, N), rng.integers(0, R, N)).astype(np.int64)
+    rows = counter.values_range(D, counter.STREAM_ROWS, 0, N * D, counter.KIND_GRAD,
+                                counter.grad_scale(1e-2)).reshape(N, D)
+    step, iota = 1000, 3
+    tokens = step - rng.integers(0, 6, K)
+    tag = workload.tag_values(5, np.arange(R), step)
+    w, _, _ = oracle.token_weights(tokens, step, iota)
+    table0, slots0 = _table_and_state(R, D, opt, 5)
+    d_in = (dev(ids), dev(rows), dev(off), dev(w), dev(tokens))
+    sep = _sparse_step(*d_in, step, iota, R, tag, decay, opt, False, True, table0, slots0)
+    fus = _sparse_step(*d_in, step, iota, R, tag, decay, opt, True, False, table0, slots0)
+    assert sep["err"] == 0 and fus["err"] == 0
+    U = int(sep["num_unique"][0])
+    assert int(fus["num_unique"][0]) == U
+    for k in ("unique_ids", "contrib_count", "active_count"):
+        assert_exact(fus[k][:U], sep[k][:U], k)
+    assert torch.equal(fus["table"], sep["table"])
+    assert all(torch.equal(a, b) for a, b in zip(fus["slots"], sep["slots"]))
+    if decay == "id_tag":
+        assert_exact(fus["tag"], sep["tag"], "tag")
