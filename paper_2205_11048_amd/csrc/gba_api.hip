@@ -237,7 +237,8 @@ static gba_status sparse_call(const int64_t* ids, const float* rows, const int64
   const uint32_t* vals = nullptr;
   // with the hot-key plan the frequent IDs are reduced apart from the rest
   SortHot hot;
-  hipError_t e = launch_sort_ids(ids, N, R, plan, ws, &keys, &vals, err, stream, plan.hot ? &hot : nullptr);
+  uint32_t* idle = nullptr;
+  hipError_t e = launch_sort_ids(ids, N, R, plan, ws, &keys, &vals, err, stream, plan.hot ? &hot : nullptr, &idle);
   if (e != hipSuccess) return GBA_ERR_HIP;
 
   SegmentArgs a;
@@ -247,6 +248,7 @@ static gba_status sparse_call(const int64_t* ids, const float* rows, const int64
   }
   a.keys = keys;
   a.vals = vals;
+  a.weights = reinterpret_cast<float*>(idle);
   a.rows = rows;
   a.offsets = contrib_offsets;
   a.w = w;

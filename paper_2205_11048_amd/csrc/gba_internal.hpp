@@ -86,11 +86,12 @@ struct SortHot {
 };
 // Sorts ids (int64 [n], each checked against [0, R)) by value, stably.  The
 // sorted keys and original occurrence indices are returned through
-// *keys_out / *vals_out, which point into `ws`.  With `split` non-null and
+// *keys_out / *vals_out, which point into `ws`; *idle_out (may be null) is an
+// array of n words in `ws` that holds no output.  With `split` non-null and
 // the hot-key plan, the output is split as described above.
 hipError_t launch_sort_ids(const int64_t* ids, int64_t n, int64_t R, const SortPlan& plan, void* ws,
                            const uint32_t** keys_out, const uint32_t** vals_out, int32_t* err,
-                           hipStream_t stream, SortHot* split = nullptr);
+                           hipStream_t stream, SortHot* split = nullptr, uint32_t** idle_out = nullptr);
 
 // ---- segments over the sorted keys: dedup, counts, decayed weighted sums
 // Fused row apply: the optimiser runs on each active row (W_r > 0) as its
@@ -107,6 +108,7 @@ struct RowApply {
 struct SegmentArgs {
   const uint32_t* keys;        // sorted IDs [N]
   const uint32_t* vals;        // occurrence index of each sorted entry [N]
+  float* weights;              // scratch [N]: the weight of each sorted entry whose weight is neither 0 nor 1
   const float* rows;           // [N][D]
   const int64_t* offsets;      // [K+1]
   const float* w;              // [K]

@@ -946,7 +946,7 @@ SortPlan plan_sort(int64_t n, int64_t R, int hot_mode) {
 
 hipError_t launch_sort_ids(const int64_t* ids, int64_t n, int64_t R, const SortPlan& plan, void* ws,
                            const uint32_t** keys_out, const uint32_t** vals_out, int32_t* err,
-                           hipStream_t stream, SortHot* split) {
+                           hipStream_t stream, SortHot* split, uint32_t** idle_out) {
   const SortLayout L = sort_layout(n, plan.blocks, plan.hot);
   char* p = static_cast<char*>(ws);
   uint32_t* keys[3] = {reinterpret_cast<uint32_t*>(p + L.off_keys0), reinterpret_cast<uint32_t*>(p + L.off_keys1),
@@ -1059,6 +1059,7 @@ hipError_t launch_sort_ids(const int64_t* ids, int64_t n, int64_t R, const SortP
   }
   *keys_out = keys[cur];
   *vals_out = vals[cur];
+  if (idle_out) *idle_out = vals[cur == 1 ? 0 : 1];
   return hipSuccess;
 }
 

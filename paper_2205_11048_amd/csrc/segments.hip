@@ -211,22 +211,6 @@ __device__ __forceinline__ int contribution_of(const int32_t* s_off, const int32
   return m < K ? m : K - 1;
 }
 
-// The same from the int64 offsets in global memory (rare path).
-__device__ __forceinline__ int contribution_global(const int64_t* off, int K, uint32_t j) {
-  int lo = 1, len = K;
-  while (len > 0) {
-    const int half = len >> 1;
-    if (off[lo + half] <= (int64_t)j) {
-      lo += half + 1;
-      len -= half + 1;
-    } else {
-      len = half;
-    }
-  }
-  const int m = lo - 1;
-  return m < 0 ? 0 : (m < K ? m : K - 1);
-}
-
 // The optimiser on one lane's 4 floats of a row (mode 1 Adagrad, 2 Adam), with
 // the row apply's arithmetic.
 __device__ __forceinline__ void update4(int mode, const OptF32& c, f32x4& pv, f32x4& s1, f32x4& s2, f32x4 g) {
@@ -594,6 +578,8 @@ seg_meta_kernel(SegmentArgs a, RunHeads heads, const int32_t* __restrict__ bucke
       }
     }
     uint32_t word[kMetaPer];
+    float weight[kMetaPer];
+    bool any_nonunit = false;
     uint32_t nheads = 0, head_bits = 0;
 #pragma unroll
     for (int e = 0; e < kMetaPer; ++e) {
@@ -613,6 +599,8 @@ seg_meta_kernel(SegmentArgs a, RunHeads heads, const int32_t* __restrict__ bucke
       }
       word[e] = (jv[e] & kIndexMask) | (head ? kHead : 0u) | (newc ? kNewC : 0u) |
                 (wt == 0.0f ? kZeroW : 0u) | ((wt != 0.0f && wt != 1.0f) ? kNonUnit : 0u);
+      weight[e] = wt;
+      any_nonunit |= wt != 0.0f && wt != 1.0f;
       nheads += head ? 1u : 0u;
       head_bits |= head ? (1u << e) : 0u;
     }
@@ -622,6 +610,9 @@ seg_meta_kernel(SegmentArgs a, RunHeads heads, const int32_t* __restrict__ bucke
 #pragma unroll
       for (int e = 0; e < kMetaPer; ++e)
         if (p0 + e < n) packed[p0 + e] = word[e];
+    }
+    if (any_nonunit) {   // the row pass reads weights other than 0 and 1 (the array is padded to 64 entries)
+      *reinterpret_cast<f32x4*>(a.weights + p0) = f32x4{weight[0], weight[1], weight[2], weight[3]};
     }
     // segment numbers: the tile's base, the waves before, the lanes before
     const uint32_t incl = wave_inclusive_scan(nheads);
@@ -722,7 +713,7 @@ seg_meta_kernel(SegmentArgs a, RunHeads heads, const int32_t* __restrict__ bucke
 // D = 16 with Adam 219 against 104 + 119, D = 64 with Adagrad 137 against 63 +
 // 74 (both storing the means too), so every width applies its rows here.
 template <int LPR, int APPLY>
-__global__ void __launch_bounds__(kSegBlock)
+__global__ void __launch_bounds__(kSegBlock) __attribute__((amdgpu_waves_per_eu(4)))
 seg_rows_kernel(SegmentArgs a, const uint32_t* __restrict__ packed, const uint32_t* __restrict__ base, int span,
                 int bshift, SegPartials part, const uint32_t* __restrict__ seg_start,
                 const uint32_t* __restrict__ cnum) {
@@ -838,7 +829,7 @@ seg_rows_kernel(SegmentArgs a, const uint32_t* __restrict__ packed, const uint32
     };
     // positions u0 .. u0 + kPart - 1 of the batch, their rows in rv[0 .. kPart)
     auto sum_batch = [&](int i0, int u0, const uint32_t (&word)[kBatch], const uint32_t (&kk)[kBatch],
-                         f32x4 (&rv)[kPart], uint32_t use, bool weighted) {
+                         f32x4 (&rv)[kPart], uint32_t use, bool weighted, f32x4 wv) {
 #pragma unroll
       for (int v = 0; v < kPart; ++v)
         if (!((use >> (u0 + v)) & 1u)) rv[v] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -899,9 +890,7 @@ seg_rows_kernel(SegmentArgs a, const uint32_t* __restrict__ packed, const uint32
           if (!weighted) {
             acc += widen(rv[v]);
           } else if (!zero) {
-            double wd = 1.0;
-            if (word[u] & kNonUnit)   // a weight other than 0 or 1: look up its contribution
-              wd = (double)a.w[contribution_global(a.offsets, a.K, word[u] & kIndexMask)];
+            const double wd = (word[u] & kNonUnit) ? (double)wv[v] : 1.0;
             acc = fma_widen(wd, rv[v], acc);
           }
           const int nc = (word[u] & kNewC) ? 1 : 0;
@@ -972,9 +961,12 @@ seg_rows_kernel(SegmentArgs a, const uint32_t* __restrict__ packed, const uint32
       load_words(i0, word);
       if (APPLY) load_keys(i0, kk);
       if (i0 == 0) first_open = !(word[0] & kHead);
-      // weights other than 0 and 1 are rare: unless some position of the
-      // wave's batch has one, rows are added without a multiply (a weight-0
-      // row is zeroed), a branch the whole wave takes together
+      // unless some position of the wave's batch has a weight other than 0
+      // and 1, rows are added without a multiply (a weight-0 row is zeroed),
+      // a branch the whole wave takes together; such weights are read from
+      // where the position pass left them (a search of the offsets in global
+      // memory per position before: D = 128, 300,007 positions of fractional
+      // weights 71 us, now 40)
       bool nonunit = false;
 #pragma unroll
       for (int u = 0; u < kBatch; ++u) nonunit |= i0 + u < nvalid && (word[u] & kNonUnit);
@@ -983,8 +975,10 @@ seg_rows_kernel(SegmentArgs a, const uint32_t* __restrict__ packed, const uint32
 #pragma unroll
       for (int u0 = 0; u0 < kBatch; u0 += kPart) {
         f32x4 rv[kPart];
+        f32x4 wv = {1.f, 1.f, 1.f, 1.f};
+        if (weighted) wv = *reinterpret_cast<const f32x4*>(a.weights + (i0 < nvalid ? p0 + i0 + u0 : 0));
         gather(i0, u0, word, rv, use);
-        sum_batch(i0, u0, word, kk, rv, use, weighted);
+        sum_batch(i0, u0, word, kk, rv, use, weighted, wv);
         if (kPark)
           while (parked >= kPop) pop(kPop);
       }

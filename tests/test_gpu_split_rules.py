@@ -111,3 +111,24 @@ def test_fused_apply_at_the_other_widths(D, opt, decay):
     assert all(torch.equal(a, b) for a, b in zip(fus["slots"], sep["slots"]))
     if decay == "id_tag":
         assert_exact(fus["tag"], sep["tag"], "tag")
+
+
+@pytest.mark.parametrize("plan", [gba.SORT_PLAIN, gba.SORT_HOT])
+@pytest.mark.parametrize("R", [200, 70_000])
+@pytest.mark.parametrize("N", [1, 6, 1027, 40_001])
+def test_fractional_weights_at_the_ends_of_the_input(N, R, plan):
+    """Weights other than 0 and 1 go from the position pass to the row pass
+    through an array of the sort (one pass at R = 200, three at 70,000): inputs
+    that end inside a lane's four positions, with 0, 1 and fractions side by
+    side, some batches without any fraction."""
+    K, D = 8, 8
+    rng = np.random.default_rng(N + R)
+    ids = rng.integers(0, R, N).astype(np.int64)
+    ids[rng.random(N) < 0.2] = R // 2
+    cut = np.sort(rng.integers(0, N + 1, K - 1))
+    off = np.concatenate([[0], cut, [N]]).astype(np.int64)
+    rows = counter.values_range(N, counter.STREAM_ROWS, 0, N * D, counter.KIND_DYADIC).reshape(N, D)
+    tokens = np.full(K, 10)
+    w = np.array([1.0, 0.5, 0.0, 1.0, 0.25, 0.0, 1.0, 0.75], np.float32)
+    res = _run_sparse(ids, rows, off, w, tokens, 10, 2, R, plan=plan)
+    _check_sparse(res, ids, rows, off, w, tokens, 10, 2, expect_exact=True)
