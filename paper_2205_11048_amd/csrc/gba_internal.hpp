@@ -64,6 +64,7 @@ struct SortPlan {
   int passes;
   int first_bits;        // cold digit bits of the first pass (the later passes take 8)
   bool hot;              // hot-key plan: frequent IDs placed by the first pass
+  bool small;            // the small sort (plain plan below 2^22 keys)
   int hot_cap;           // most hot IDs (hot plan)
   int64_t blocks;        // tiles of the first pass (the most of any pass)
   size_t bytes;          // workspace bytes
@@ -84,6 +85,12 @@ struct SortHot {
   const uint32_t* meta = nullptr;       // [0] = H
   int bshift = 0;
 };
+// The plain plan below kSmallSortBelow keys (sort_small.hip).
+constexpr int64_t kSmallSortBelow = int64_t(1) << 22;
+size_t small_sort_bytes(int64_t n, int key_bits);
+hipError_t launch_small_sort(const int64_t* ids, int64_t n, int64_t R, int key_bits, void* ws, const uint32_t** keys_out,
+                             const uint32_t** vals_out, uint32_t** idle_out, int32_t* err, hipStream_t stream);
+
 // Sorts ids (int64 [n], each checked against [0, R)) by value, stably.  The
 // sorted keys and original occurrence indices are returned through
 // *keys_out / *vals_out, which point into `ws`; *idle_out (may be null) is an

@@ -25,6 +25,7 @@
 // element; which IDs are hot changes only the time it takes.
 #include "gba_device.hpp"
 #include "gba_internal.hpp"
+#include "sort_device.hpp"
 
 namespace gba {
 
@@ -37,14 +38,9 @@ constexpr int kSortWaves = kSortBlock / kWave;
 constexpr int kItemsFirst = 8;
 constexpr int kItemsRest = 16;
 constexpr int kItemsHotFirst = 8;   // the first pass of the hot-key plan
-// Below this many keys the plain plan keeps 2048-key tiles on every pass: the
-// later passes then have twice the blocks (at 256 K keys, 125 instead of 63
-// for 256 compute units), where long write runs matter less than filling the chip.
-constexpr int64_t kNarrowTilesBelow = int64_t(1) << 20;
 template <int ITEMS>
 constexpr int64_t tile_keys() { return (int64_t)kSortBlock * ITEMS; }
 constexpr int kRadix = 256;
-constexpr int kXcds = 8;   // MI355X: 8 accelerator dies, each with its own L2
 // Tiles per chunk (one hist block): one per wave, or four per wave where a
 // pass has tiles enough (the digit scans then read a quarter of the chunk
 // rows, while small passes keep their hist blocks spread over the chip).
@@ -59,6 +55,7 @@ constexpr int kHotCap = 254;           // most hot IDs (one bin each; the lookup
 constexpr int kHotBuckets = 1024;      // lookup buckets over the top 10 key bits
 constexpr uint32_t kHotMinCount = 4;   // a sampled ID must occur this often to be hot
 constexpr int64_t kHotMinKeys = int64_t(1) << 22;   // below this the plain sort is used
+static_assert(kHotMinKeys == kSmallSortBelow, "the plain plan below the hot plan's sizes is the small sort");
 
 // Pass kinds.
 enum : int {
@@ -127,57 +124,6 @@ static HotTables hot_tables(char* ws, const SortLayout& L, int key_bits) {
   t.digit = reinterpret_cast<uint8_t*>(ws + L.off_digit);
   t.bshift = key_bits > 10 ? key_bits - 10 : 0;
   return t;
-}
-
-// Mask of the active lanes whose digit equals this lane's digit.  Per bit,
-// the lanes that differ from this one are the ballot of the bit, flipped
-// where this lane's bit is 1: ballot ^ (0 or all ones), OR-ed into a mask of
-// mismatches (one sign-extending bit extract, a compare for the ballot and
-// one three-input bit operation per 32-lane half).
-__device__ __forceinline__ uint64_t match_digit(uint32_t digit, int bits, bool active) {
-  uint32_t diff_lo, diff_hi;
-  {
-    const uint64_t on = __ballot(active);
-    diff_lo = ~(uint32_t)on;
-    diff_hi = ~(uint32_t)(on >> 32);
-  }
-  for (int b = 0; b < bits; ++b) {
-    const uint32_t x = (uint32_t)((int32_t)(digit << (31 - b)) >> 31);   // 0 or all ones: the lane's bit b
-    const uint64_t bal = __ballot(x != 0u);
-    // diff | (ballot ^ x) in one gfx950 three-input bit operation (table: S0 | (S1 ^ S2))
-    diff_lo = __builtin_amdgcn_bitop3_b32(diff_lo, (uint32_t)bal, x, 0xF6);
-    diff_hi = __builtin_amdgcn_bitop3_b32(diff_hi, (uint32_t)(bal >> 32), x, 0xF6);
-  }
-  const uint64_t m = ~(((uint64_t)diff_hi << 32) | diff_lo);
-  return active ? m : 0ull;
-}
-
-// The same match for a digit width known at compile time (the loop unrolled).
-template <int BITS>
-__device__ __forceinline__ uint64_t match_digit_n(uint32_t digit, bool active) {
-  uint32_t diff_lo, diff_hi;
-  {
-    const uint64_t on = __ballot(active);
-    diff_lo = ~(uint32_t)on;
-    diff_hi = ~(uint32_t)(on >> 32);
-  }
-#pragma unroll
-  for (int b = 0; b < BITS; ++b) {
-    const uint32_t x = (uint32_t)((int32_t)(digit << (31 - b)) >> 31);
-    const uint64_t bal = __ballot(x != 0u);
-    diff_lo = __builtin_amdgcn_bitop3_b32(diff_lo, (uint32_t)bal, x, 0xF6);
-    diff_hi = __builtin_amdgcn_bitop3_b32(diff_hi, (uint32_t)(bal >> 32), x, 0xF6);
-  }
-  const uint64_t m = ~(((uint64_t)diff_hi << 32) | diff_lo);
-  return active ? m : 0ull;
-}
-
-// A copy of x that the compiler cannot tie to earlier uses of x, so values
-// derived from it (LDS addresses) are recomputed where needed instead of
-// being held in registers across a phase.
-__device__ __forceinline__ uint32_t opaque(uint32_t x) {
-  asm volatile("" : "+v"(x));
-  return x;
 }
 
 // Number of hot IDs below `key`, and whether `key` is one of them.  The bucket
@@ -573,15 +519,6 @@ sort_digit_scan_kernel(uint32_t* __restrict__ chunk, int64_t nchunks, uint32_t* 
   if (threadIdx.x == 0) total[d] = all;
 }
 
-// Tile of scatter block b.  Blocks are dispatched round-robin over the 8 XCDs
-// (block b on XCD b % 8); giving XCD x the x-th eighth of the tiles, in order,
-// puts neighbouring tiles on one L2, which then merges their partial-line
-// writes into the same digit bucket before they reach HBM.
-__device__ __forceinline__ int64_t xcd_tile(int64_t b, int64_t tiles) {
-  const int64_t x = b % kXcds, i = b / kXcds, q = tiles / kXcds, r = tiles % kXcds;
-  return x * q + (x < r ? x : r) + i;
-}
-
 // Tile of scatter block b with the tiles handed to the XCDs in chunks of C
 // consecutive tiles (chunk c on XCD c % 8), for the 8-bit passes: all XCDs
 // write inside one window of each digit's output (fewer, denser write
@@ -939,6 +876,11 @@ SortPlan plan_sort(int64_t n, int64_t R, int hot_mode) {
     const int cold_bins = 1 << hot_first;
     p.hot_cap = kRadix - cold_bins < kHotCap ? kRadix - cold_bins : kHotCap;
   }
+  p.small = !hot && n < kSmallSortBelow;
+  if (p.small) {
+    p.bytes = small_sort_bytes(n, bits);
+    return p;
+  }
   p.blocks = n > 0 ? ceil_div(n, tile_keys<kItemsFirst>()) : 0;
   p.bytes = sort_layout(n, p.blocks, p.hot).bytes;
   return p;
@@ -947,6 +889,10 @@ SortPlan plan_sort(int64_t n, int64_t R, int hot_mode) {
 hipError_t launch_sort_ids(const int64_t* ids, int64_t n, int64_t R, const SortPlan& plan, void* ws,
                            const uint32_t** keys_out, const uint32_t** vals_out, int32_t* err,
                            hipStream_t stream, SortHot* split, uint32_t** idle_out) {
+  if (plan.small) {
+    if (split) *split = SortHot{};
+    return launch_small_sort(ids, n, R, plan.key_bits, ws, keys_out, vals_out, idle_out, err, stream);
+  }
   const SortLayout L = sort_layout(n, plan.blocks, plan.hot);
   char* p = static_cast<char*>(ws);
   uint32_t* keys[3] = {reinterpret_cast<uint32_t*>(p + L.off_keys0), reinterpret_cast<uint32_t*>(p + L.off_keys1),
@@ -981,7 +927,6 @@ hipError_t launch_sort_ids(const int64_t* ids, int64_t n, int64_t R, const SortP
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   int cur = 0;
-  const bool narrow = !plan.hot && n < kNarrowTilesBelow;
   // the narrowest digit goes first: the first pass sees keys in arrival order,
   // and fewer bins there mean longer runs of equal digits to write
   const int first_bits = plan.first_bits;
@@ -994,7 +939,7 @@ hipError_t launch_sort_ids(const int64_t* ids, int64_t n, int64_t R, const SortP
     const int out = pass == 0 ? 0 : (gap ? 2 : 1 - cur);
     const void* kin = pass == 0 ? (const void*)ids : (const void*)keys[cur];
     const int64_t tiles =
-        ceil_div(n, pass > 0 ? (narrow ? tile_keys<kItemsFirst>() : tile_keys<kItemsRest>())
+        ceil_div(n, pass > 0 ? tile_keys<kItemsRest>()
                              : (plan.hot ? tile_keys<kItemsHotFirst>() : tile_keys<kItemsFirst>()));
     const int tpw = hist_tiles_per_wave(tiles);
     const int chunk_tiles = kSortWaves * tpw;
@@ -1015,8 +960,6 @@ hipError_t launch_sort_ids(const int64_t* ids, int64_t n, int64_t R, const SortP
       GBA_HIST(true, kItemsFirst, kPlain, (const uint32_t*)nullptr)
     } else if (plan.hot) {
       GBA_HIST(false, kItemsRest, kCold, n_cold)
-    } else if (narrow) {
-      GBA_HIST(false, kItemsFirst, kPlain, (const uint32_t*)nullptr)
     } else {
       GBA_HIST(false, kItemsRest, kPlain, (const uint32_t*)nullptr)
     }
@@ -1044,11 +987,6 @@ hipError_t launch_sort_ids(const int64_t* ids, int64_t n, int64_t R, const SortP
       hipLaunchKernelGGL((sort_scatter_kernel<false, kItemsRest, kCold>), grid, block, 0, stream, kin, vin,
                          keys[out], vals[out], (uint32_t*)nullptr, (uint32_t*)nullptr, n, n_cold, n, shift, bits,
                          R, (const uint32_t*)hist, (const uint32_t*)chunk, (const uint32_t*)total, ht, chunk_shift);
-    else if (narrow)
-      hipLaunchKernelGGL((sort_scatter_kernel<false, kItemsFirst, kPlain>), grid, block, 0, stream, kin, vin,
-                         keys[out], vals[out], (uint32_t*)nullptr, (uint32_t*)nullptr, n, (const uint32_t*)nullptr,
-                         n, shift, bits, R, (const uint32_t*)hist, (const uint32_t*)chunk, (const uint32_t*)total,
-                         ht, chunk_shift);
     else
       hipLaunchKernelGGL((sort_scatter_kernel<false, kItemsRest, kPlain>), grid, block, 0, stream, kin, vin,
                          keys[out], vals[out], (uint32_t*)nullptr, (uint32_t*)nullptr, n, (const uint32_t*)nullptr,
