@@ -706,7 +706,10 @@ seg_meta_kernel(SegmentArgs a, RunHeads heads, const int32_t* __restrict__ bucke
 // group would store and update as its segments close while the lanes of the
 // other groups idle.  Wide rows that are only stored (two groups per wave or
 // one) are written as they close (D = 128, 300,007 positions: 71 us, parked
-// 100).  Bound: random row accesses, some 35-39 G 128-byte lines a second
+// 100).  The segments a group closes after its last position go through the
+// ring too, so the wave's last updates share two or three memory latencies
+// instead of taking two each (20,480 positions at D = 16: 20 -> 17.5 us; 6.5 M
+// at D = 32 with Adam 299 -> 291).  Bound: random row accesses, some 35-39 G 128-byte lines a second
 // read and written at every width (a read-only gather reaches 47-50); D = 32
 // with Adam, 6.5 M positions, per-ID decay: 303 us for this pass against 144 +
 // 183 + 22 for the pass, the row apply and the tags as launches of their own;
@@ -726,19 +729,17 @@ seg_rows_kernel(SegmentArgs a, const uint32_t* __restrict__ packed, const uint32
   // lane holds kPart 16-byte row pieces while they are in flight)
   constexpr int kPart = kBatchPart;
   constexpr bool kPark = APPLY != 0 || LPR <= 16;
-  constexpr int kR = LPR <= 2 ? 1 : ((APPLY == 1 && LPR >= 8) ? 4 : 2);   // rounds of rows in flight (registers)
+  constexpr int kR = LPR <= 4 ? 1 : 2;   // rounds of rows in flight (four: no faster, 128 registers instead of 108)
   constexpr int kPop = kR * GW;
-  // a part adds at most kPart * GW entries to fewer than kPop
-  constexpr int kSlots = kPark ? kPop + kPart * GW : kWave * (int)sizeof(f64x4) / (LPR * (int)sizeof(f32x4));
+  // a part, or the two segments that a group may close after its last one,
+  // adds at most kPart * GW entries to fewer than kPop
+  constexpr int kSlots = kPark ? kPop + kPart * GW : 1;
   auto ring = [](int x) { return x < kSlots ? x : x - kSlots; };   // x < 2 kSlots
-  __shared__ f32x4 s_park[kSegWaves][kSlots][LPR];
+  __shared__ f32x4 s_park[kPark ? kSegWaves : 1][kSlots][LPR];
   __shared__ uint32_t s_park_out[kPark ? kSegWaves : 1][kPark ? kSlots : 1];
   __shared__ uint32_t s_park_cw[kPark ? kSegWaves : 1][kPark ? kSlots : 1];
   __shared__ uint32_t s_park_key[APPLY ? kSegWaves : 1][APPLY ? kSlots : 1];
-  // per-lane chain sums at the end of the groups: in the parking area of the
-  // lane's own wave, free by then
-  static_assert(sizeof(s_park[0]) >= kWave * sizeof(f64x4), "chain sums fit a wave's parking area");
-  auto s_acc_at = [&](int t) -> f64x4& { return reinterpret_cast<f64x4*>(&s_park[t / kWave][0][0])[t % kWave]; };
+  __shared__ f64x4 s_acc[kSegBlock];   // per-lane chain sums at the end of the groups
   __shared__ int32_t s_cc[G], s_ww[G];
   __shared__ uint32_t s_seg[G], s_flags[G];
   __shared__ uint32_t s_cnum[kHotSlots];
@@ -784,7 +785,35 @@ seg_rows_kernel(SegmentArgs a, const uint32_t* __restrict__ packed, const uint32
     int fcc = 0, fww = 0;
     bool owner = false;
     int parked = 0, first_parked = 0;   // entries of the wave's ring, and its first (the same in every lane)
-    uint32_t cur_key = (APPLY && nvalid > 0) ? a.keys[p0] : 0u;   // row of the open segment (row apply)
+    const uint32_t key0 = (APPLY && nvalid > 0) ? a.keys[p0] : 0u;
+    uint32_t cur_key = key0;   // row of the open segment (row apply)
+    auto mean_of = [&](f64x4 sum, int count) {
+      const double div = by_k ? (double)a.K : (double)count;
+      // a segment has at most K contributions: the table covers every count when K is small
+      const double y = by_k ? recip_k : (small_k ? s_recip[count] : 1.0 / div);
+      return narrow(div_rounded(sum, div, y));
+    };
+    // A segment of this group is finished (mc: the lanes of the wave's groups
+    // that finish one at the same time; the caller adds them to `parked`).
+    auto park = [&](uint64_t mc, f32x4 g, int64_t out, int count, int active, uint32_t key) {
+      if (kPark) {
+        const uint32_t below =
+            __builtin_amdgcn_mbcnt_hi((uint32_t)(mc >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mc, 0u));
+        const int slot = ring(ring(first_parked + parked) + (int)(below / LPR));
+        if (lane_on) s_park[w][slot][gl] = g;
+        if (gl == 0) {
+          s_park_out[w][slot] = (uint32_t)out;
+          s_park_cw[w][slot] = (uint32_t)count | ((uint32_t)active << 16);
+          if (APPLY) s_park_key[w][slot] = key;
+        }
+      } else if (out >= 0 && out < N) {   // always true when the numbering is consistent
+        if (lane_on) store_stream(reinterpret_cast<f32x4*>(a.agg + out * D + gl * 4), g);
+        if (gl == 0) {
+          a.contrib_count[out] = count;
+          a.active_count[out] = active;
+        }
+      }
+    };
     // Words of the batch at i0 (the packed array is padded by a group span, so
     // whole vectors stay in bounds past the group's end).
     auto load_words = [&](int i0, uint32_t (&word)[kBatch]) {
@@ -850,30 +879,7 @@ seg_rows_kernel(SegmentArgs a, const uint32_t* __restrict__ packed, const uint32
               if (!closes) {
                 facc = acc; fcc = cc; fww = ww; owner = true;
               } else {
-                const double div = by_k ? (double)a.K : (double)cc;
-                // a segment has at most K contributions: the table covers every count when K is small
-                const double y = by_k ? recip_k : (small_k ? s_recip[cc] : 1.0 / div);
-                const f32x4 g = narrow(div_rounded(acc, div, y));
-                if (kPark) {
-                  const uint32_t below =
-                      __builtin_amdgcn_mbcnt_hi((uint32_t)(mc >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mc, 0u));
-                  const int slot = ring(ring(first_parked + parked) + (int)(below / LPR));
-                  if (lane_on) s_park[w][slot][gl] = g;
-                  if (gl == 0) {
-                    s_park_out[w][slot] = (uint32_t)(seg + hb);
-                    s_park_cw[w][slot] = (uint32_t)cc | ((uint32_t)ww << 16);
-                    if (APPLY) s_park_key[w][slot] = cur_key;
-                  }
-                } else {
-                  const int64_t out = seg + hb;
-                  if (out < N) {   // always true when the numbering is consistent
-                    if (lane_on) store_stream(reinterpret_cast<f32x4*>(a.agg + out * D + gl * 4), g);
-                    if (gl == 0) {
-                      a.contrib_count[out] = cc;
-                      a.active_count[out] = ww;
-                    }
-                  }
-                }
+                park(mc, mean_of(acc, cc), seg + hb, cc, ww, cur_key);
               }
               in_first = false;
             }
@@ -984,15 +990,12 @@ seg_rows_kernel(SegmentArgs a, const uint32_t* __restrict__ packed, const uint32
       }
     }
 
-    if (kPark)
-      while (parked > 0) pop(parked < kPop ? parked : kPop);
-
-    bool last_open = false, pass = false;
+    bool last_open = false, pass = false, last_closes = false;
     if (nvalid > 0) {
       last_open = nvalid == SPAN && (p0 + SPAN) < n && !(packed[p0 + SPAN] & kHead);
       if (last_open) {
         pass = in_first && first_open;
-        s_acc_at(threadIdx.x) = acc;
+        s_acc[threadIdx.x] = acc;
         if (gl == 0) {
           s_cc[grp] = cc;
           s_ww[grp] = ww;
@@ -1001,44 +1004,54 @@ seg_rows_kernel(SegmentArgs a, const uint32_t* __restrict__ packed, const uint32
       } else if (in_first && first_open) {
         facc = acc; fcc = cc; fww = ww; owner = true;
       } else {
-        finalize_segment(a, seg + hb, acc, cc, ww, gl, lane_on, APPLY);
+        last_closes = true;
       }
+    }
+    {
+      const uint64_t mc = kPark ? __ballot(last_closes) : 0ull;
+      if (last_closes) park(mc, mean_of(acc, cc), seg + hb, cc, ww, cur_key);
+      parked += __popcll(mc) / LPR;
     }
     if (gl == 0) s_flags[grp] = (nvalid > 0 ? kValid : 0u) | (last_open ? kOpen : 0u) | (pass ? kPass : 0u);
     __syncthreads();
 
     // a group whose first run began before it closes the chain of runs
-    if (owner) {
+    {
+      bool closes = false;
       f64x4 tot = facc;
       int tcc = fcc, tww = fww;
-      bool from_prev_tile = true;
-      for (int gg = grp - 1; gg >= 0; --gg) {
-        tot += s_acc_at(gg * LPR + gl);
-        tcc += s_cc[gg];
-        tww += s_ww[gg];
-        if (!(s_flags[gg] & kPass)) {
-          from_prev_tile = false;
-          break;
+      if (owner) {
+        for (int gg = grp - 1; gg >= 0; --gg) {
+          tot += s_acc[gg * LPR + gl];
+          tcc += s_cc[gg];
+          tww += s_ww[gg];
+          if (!(s_flags[gg] & kPass)) {
+            closes = true;
+            break;
+          }
+        }
+        if (!closes) {   // the chain began in an earlier tile
+          if (lane_on) *reinterpret_cast<f64x4*>(part.first_acc + tile * D + gl * 4) = tot;
+          if (gl == 0) {
+            part.first_cc[tile] = tcc;
+            part.first_ww[tile] = tww;
+          }
         }
       }
-      if (from_prev_tile) {
-        if (lane_on) *reinterpret_cast<f64x4*>(part.first_acc + tile * D + gl * 4) = tot;
-        if (gl == 0) {
-          part.first_cc[tile] = tcc;
-          part.first_ww[tile] = tww;
-        }
-      } else {
-        finalize_segment(a, (int64_t)gbase - 1 + hb0, tot, tcc, tww, gl, lane_on, APPLY);
-      }
+      const uint64_t mc = kPark ? __ballot(closes) : 0ull;
+      if (closes) park(mc, mean_of(tot, tcc), (int64_t)gbase - 1 + hb0, tcc, tww, key0);
+      parked += __popcll(mc) / LPR;
     }
+    if (kPark)
+      while (parked > 0) pop(parked < kPop ? parked : kPop);
     // the chain that runs into the next tile
     if (grp == G - 1 && (s_flags[G - 1] & kOpen)) {
-      f64x4 tot = s_acc_at((G - 1) * LPR + gl);
+      f64x4 tot = s_acc[(G - 1) * LPR + gl];
       int tcc = s_cc[G - 1], tww = s_ww[G - 1];
       int gg = G - 1;
       while (gg > 0 && (s_flags[gg] & kPass)) {
         --gg;
-        tot += s_acc_at(gg * LPR + gl);
+        tot += s_acc[gg * LPR + gl];
         tcc += s_cc[gg];
         tww += s_ww[gg];
       }
