@@ -8,8 +8,8 @@
 // system sees long contiguous runs per gradient wherever the caller placed
 // the K buffers (short runs from many buffers at once were measured to lose
 // up to 15% of bandwidth to DRAM row conflicts, depending on the buffers'
-// relative addresses).  Where P is too small for such blocks to give every
-// compute unit one, threads take 4 vectors (or 1) instead of 16.  Each thread
+// relative addresses).  Threads take fewer vectors than 16 where such blocks
+// would leave part of the chip idle at the end (dense_vecs).  Each thread
 // accumulates its vectors in float64 in buffer order, so the only rounding is
 // the final one to float.
 #include <algorithm>
@@ -22,9 +22,6 @@ namespace gba {
 
 constexpr int kDenseBlock = 256;                                      // elementwise optimiser kernels
 constexpr int kSumBlock = 512;                                        // the reduction: 8 waves
-// f32x4 per thread: 16 (each wave reads 16 KB of one gradient in a row); 4 or
-// 1 where P is too small for 16 to give every compute unit a block
-constexpr int kDenseVecs = 16;
 template <int VECS>
 constexpr int64_t dense_span() { return (int64_t)kSumBlock * VECS; }   // vectors per block step
 constexpr int64_t kDenseMaxBlocks = 65535;
@@ -114,8 +111,8 @@ __device__ __forceinline__ void finish_scalar(const float* const* grads, const u
 
 // Vectors q[j] = vb + 64 j (j < VECS, q < nvec) are finished: g in
 // float first (which frees the float64 sums), then the optimiser, with the
-// state of a whole group of vectors requested at once (16 for Adagrad, 8 for
-// Adam: what fits the registers the sums held), so a block's finishing costs
+// state of a whole group of vectors requested at once (all for Adagrad, 8 at
+// most for Adam: what fits the registers the sums held), so a block's finishing costs
 // one or two memory latencies, not one per vector.
 template <int MODE, int VECS>
 __device__ __forceinline__ void finish_vectors(const f64x4* acc, double denom, int64_t vb, int64_t nvec,
@@ -129,7 +126,8 @@ __device__ __forceinline__ void finish_vectors(const f64x4* acc, double denom, i
       if (vb + kWave * j < nvec) store_stream(reinterpret_cast<f32x4*>(out) + vb + kWave * j, g[j]);
   }
   if (MODE == kStoreOnly) return;
-  constexpr int kGroup = (MODE == kApplyAdam) ? (VECS < 8 ? VECS : 8) : VECS;
+  constexpr int kGroup = (MODE == kApplyAdam && VECS > 8) ? VECS / 2 : VECS;
+  static_assert(VECS % kGroup == 0, "whole groups");
 #pragma unroll
   for (int j0 = 0; j0 < VECS; j0 += kGroup) {
     f32x4 pv[kGroup], sv[kGroup], vv[kGroup];
@@ -262,13 +260,35 @@ static int device_cus() {
   return cus;
 }
 
-// Vectors per thread for P elements: the most that still give every compute
-// unit a block step.
+// Vectors per thread for P elements (f32x4; a wave reads that many KB of one
+// gradient in a row).  A compute unit takes one block step after another, so
+// the call lasts about ceil(steps / cus) steps of vecs: the choice is the vecs
+// that makes this least, the larger of two equal ones (longer runs), but never
+// 8, whose single step per compute unit keeps too few loads in flight where
+// two steps of 4 are the same work (P = 4 M, K = 32: 99 us against 92).  From
+// four vectors for every thread of the chip on, at least 4.  Measured, us with
+// 16 (4 or 1 where 16 left compute units without a step) against this rule,
+// Adagrad, K = 64 or 100: P = 2 M 95 and 83, 4.2 M 295 and 265, 6 M 397 and
+// 388, 8 M 532 and 520, 12 M 538 and 510, 20 M 882 and 810.
 static int dense_vecs(int64_t P, int cus) {
+  constexpr int kFew[] = {4, 3, 2, 1};
+  constexpr int kMany[] = {16, 14, 12, 10, 6, 4};
   const int64_t nvec = P / 4;
-  if (cus <= 0 || ceil_div(nvec, dense_span<kDenseVecs>()) >= cus) return kDenseVecs;
-  if (ceil_div(nvec, dense_span<4>()) >= cus) return 4;
-  return 1;
+  if (cus <= 0) return 16;
+  int best = 0;
+  int64_t best_cost = 0;
+  auto consider = [&](int v) {
+    const int64_t cost = ceil_div(ceil_div(nvec, (int64_t)kSumBlock * v), cus) * v;
+    if (best == 0 || cost < best_cost) {
+      best = v;
+      best_cost = cost;
+    }
+  };
+  if (nvec < dense_span<4>() * cus)
+    for (int v : kFew) consider(v);
+  else
+    for (int v : kMany) consider(v);
+  return best;
 }
 
 template <int MODE, bool CARRY, int VECS>
@@ -297,11 +317,20 @@ static hipError_t launch_dense_mode(const float* const* grads, const float* w, i
   if (P <= 0) return hipSuccess;
   const int cus = device_cus();
   switch (dense_vecs(P, cus)) {
-    case 1: return launch_dense_vecs<MODE, CARRY, 1>(grads, w, K, P, out, st, run, denom, reset, cus, stream);
-    case 4: return launch_dense_vecs<MODE, CARRY, 4>(grads, w, K, P, out, st, run, denom, reset, cus, stream);
-    default:
-      return launch_dense_vecs<MODE, CARRY, kDenseVecs>(grads, w, K, P, out, st, run, denom, reset, cus, stream);
+#define GBA_DENSE_VECS(V) \
+  case V: return launch_dense_vecs<MODE, CARRY, V>(grads, w, K, P, out, st, run, denom, reset, cus, stream);
+    GBA_DENSE_VECS(1)
+    GBA_DENSE_VECS(2)
+    GBA_DENSE_VECS(3)
+    GBA_DENSE_VECS(4)
+    GBA_DENSE_VECS(6)
+    GBA_DENSE_VECS(10)
+    GBA_DENSE_VECS(12)
+    GBA_DENSE_VECS(14)
+    GBA_DENSE_VECS(16)
+#undef GBA_DENSE_VECS
   }
+  return hipErrorInvalidValue;
 }
 
 template <int MODE, bool CARRY>
@@ -309,9 +338,19 @@ static int64_t launch_count(int64_t P, int32_t K) {
   const int cus = device_cus();
   int64_t steps = 0, round = 0;
   switch (dense_vecs(P, cus)) {
-    case 1: dense_rounds<MODE, CARRY, 1>(P, K, cus, &steps, &round); break;
-    case 4: dense_rounds<MODE, CARRY, 4>(P, K, cus, &steps, &round); break;
-    default: dense_rounds<MODE, CARRY, kDenseVecs>(P, K, cus, &steps, &round); break;
+#define GBA_DENSE_VECS(V) \
+  case V: dense_rounds<MODE, CARRY, V>(P, K, cus, &steps, &round); break;
+    GBA_DENSE_VECS(1)
+    GBA_DENSE_VECS(2)
+    GBA_DENSE_VECS(3)
+    GBA_DENSE_VECS(4)
+    GBA_DENSE_VECS(6)
+    GBA_DENSE_VECS(10)
+    GBA_DENSE_VECS(12)
+    GBA_DENSE_VECS(14)
+    GBA_DENSE_VECS(16)
+#undef GBA_DENSE_VECS
+    default: return 0;
   }
   return ceil_div(steps, round);
 }
