@@ -80,6 +80,13 @@ static int rows_span(int64_t N, int lpr) {
   const int64_t waves = N * lpr / ((int64_t)kWave * 32);   // of a pass with spans of 32
   return waves >= 2048 ? 32 : (waves >= 1024 ? 16 : 8);
 }
+// The same for the hot IDs' pass: 32 below 2^25 occurrences, where chunks of
+// 128 per group leave less than a round of blocks for the chip (the pass and
+// its finish, us: 6.5 M occurrences at D = 32 125 + 7 with 128, 93 + 9 with 64,
+// 88 + 11 with 32; 10 M at D = 16 170 + 8, 164 + 9, 154 + 11).  Above, 64 takes
+// from the pass what the joining of twice the chunks costs (783 + 20, 770 +
+// 32).  Below the sizes that choose hot IDs by themselves 128 keeps the scratch small.
+static int hot_span(int64_t N) { return N >= (int64_t(1) << 25) || N < kSmallSortBelow ? kGroupSpan : 32; }
 // The segment count is kept at the start of every group.
 static int base_shift(int span) { return span >= 32 ? 5 : (span == 16 ? 4 : 3); }
 static_assert(kBaseSpan == 1 << 5, "base_shift");
@@ -114,7 +121,7 @@ constexpr int kRecipMax = 256;   // divisors with a reciprocal in the row pass's
 
 struct SegLayout {
   int64_t meta_tiles, row_tiles, hot_chunks;
-  int span;              // positions per lane group of the row pass
+  int span, hot_span;    // positions per lane group of the row pass and of the hot IDs' pass
   size_t off_heads, off_buckets, off_packed, off_base, off_cnt, off_first_acc, off_last_acc, off_fix, off_start,
       off_cnum, off_hot_acc, off_hot_cnt, bytes;
 };
@@ -142,7 +149,8 @@ static SegLayout seg_layout(int64_t N, int32_t D) {
   // the cold positions below it
   L.off_cnum = o;      o += align_up(3 * (kHotSlots + 1) * 4);
   // per chunk of a hot run: float64 sums and (contributions, active, first and last contribution)
-  L.hot_chunks = (N > 0 ? ceil_div(N, rows_tile(lpr, kGroupSpan)) : 1) + kHotSlots;
+  L.hot_span = hot_span(N);
+  L.hot_chunks = (N > 0 ? ceil_div(N, rows_tile(lpr, L.hot_span)) : 1) + kHotSlots;
   // (the run-head groups' counts lie here too: they are last read by the
   // position pass, before the hot sums are written; hot_chunks * D * 8 is at
   // least N / 1024 + 8192 bytes, the groups take at most N / 4096 + 4096)
@@ -1201,10 +1209,10 @@ __device__ __forceinline__ float row_weight(const SegmentArgs& a, const float* s
 
 template <int LPR>
 __global__ void __launch_bounds__(kSegBlock)
-hot_rows_kernel(SegmentArgs a, const int32_t* __restrict__ buckets, int q, int nbuckets, HotPartials hp) {
+hot_rows_kernel(SegmentArgs a, const int32_t* __restrict__ buckets, int q, int nbuckets, int span, HotPartials hp) {
   constexpr int GW = kWave / LPR;            // groups per wave
   constexpr int G = kSegWaves * GW;          // groups per block
-  constexpr int64_t TILE = (int64_t)G * kGroupSpan;
+  const int64_t TILE = (int64_t)G * span;
   extern __shared__ int32_t s_dyn[];
   __shared__ uint32_t s_cp[kHotSlots + 1];
   __shared__ uint32_t s_tmp[kSegWaves + 1];
@@ -1245,9 +1253,9 @@ hot_rows_kernel(SegmentArgs a, const int32_t* __restrict__ buckets, int q, int n
   const int gl = lane % LPR;
   const int grp = w * GW + lane / LPR;
   const bool lane_on = gl * 4 < D;
-  const int64_t p0 = c0 + (int64_t)grp * kGroupSpan;
+  const int64_t p0 = c0 + (int64_t)grp * span;
   const int64_t left = (p0 < run_end) ? run_end - p0 : 0;
-  const int nvalid = left >= kGroupSpan ? kGroupSpan : (int)left;
+  const int nvalid = left >= span ? span : (int)left;
   f64x4 acc = {0.0, 0.0, 0.0, 0.0};
   int cg = 0, ag = 0, first = -1, last = -1;
   for (int i0 = 0; i0 < nvalid; i0 += kBatch) {
@@ -1491,7 +1499,7 @@ static hipError_t launch_rows(const SegmentArgs& a, const uint32_t* packed, cons
   if (a.n_dev) {
     const size_t lds = (size_t)(3 * a.K + 1 + nb) * sizeof(int32_t);
     hipLaunchKernelGGL(hot_rows_kernel<LPR>, dim3((unsigned)L.hot_chunks), dim3(kSegBlock), lds, stream, a, buckets,
-                       q, nb, hp);
+                       q, nb, L.hot_span, hp);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (a.N >= (int64_t(1) << 25))
       hipLaunchKernelGGL((hot_finish_kernel<LPR, 1024>), dim3(kHotSlots), dim3(1024), 0, stream, a, hp, cnum,
