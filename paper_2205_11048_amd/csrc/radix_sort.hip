@@ -9,6 +9,7 @@
 // digit; and a scatter in which each tile adds up its own offsets (digit
 // start + chunk prefix + the tiles before it in its chunk), ranks its keys
 // stably in LDS and writes runs of equal digits together.
+// (The plain plan below 2^22 keys is in sort_small.hip.)
 // Ranks inside a wave come from ballots that match lanes holding the same
 // digit, so skewed (Zipf) keys cost no LDS atomics on hot bins in the scatter.
 //

@@ -737,17 +737,35 @@ seg_rows_kernel(SegmentArgs a, const uint32_t* __restrict__ packed, const uint32
   // lane holds kPart 16-byte row pieces while they are in flight)
   constexpr int kPart = kBatchPart;
   constexpr bool kPark = APPLY != 0 || LPR <= 16;
-  constexpr int kR = LPR <= 4 ? 1 : 2;   // rounds of rows in flight (four: no faster, 128 registers instead of 108)
+  // Rounds of rows in flight: what 128 registers and 40 KB of LDS per block
+  // (four waves per SIMD) allow.  Four rounds leave no LDS for chain sums of
+  // their own (kOwnAcc): those then share the ring, which has to be emptied
+  // once more.  Measured in turn in one process: Adagrad, D = 32, 65.5 M
+  // positions 3399 us with four rounds, 3416 with two and sums of their own; D =
+  // 64, a step of 852 K 249 and 254; where two rounds are the most either way
+  // the sums of their own win (D = 32 with Adam, 6.5 M positions 612 and 618;
+  // D = 16, a step of 20,480 56 and 58).
+  constexpr bool kOwnAcc = !(APPLY == 1 && LPR >= 8);
+  constexpr int kR = LPR <= 4 ? 1 : (kOwnAcc ? 2 : 4);
   constexpr int kPop = kR * GW;
   // a part, or the two segments that a group may close after its last one,
   // adds at most kPart * GW entries to fewer than kPop
+  constexpr int kAccSlots = kWave * (int)sizeof(f64x4) / (LPR * (int)sizeof(f32x4));   // entries that hold a wave's chain sums
   constexpr int kSlots = kPark ? kPop + kPart * GW : 1;
   auto ring = [](int x) { return x < kSlots ? x : x - kSlots; };   // x < 2 kSlots
   __shared__ f32x4 s_park[kPark ? kSegWaves : 1][kSlots][LPR];
   __shared__ uint32_t s_park_out[kPark ? kSegWaves : 1][kPark ? kSlots : 1];
   __shared__ uint32_t s_park_cw[kPark ? kSegWaves : 1][kPark ? kSlots : 1];
   __shared__ uint32_t s_park_key[APPLY ? kSegWaves : 1][APPLY ? kSlots : 1];
-  __shared__ f64x4 s_acc[kSegBlock];   // per-lane chain sums at the end of the groups
+  // per-lane chain sums at the end of the groups, in their own array or in the
+  // last entries of the ring of the lane's own wave, which is empty by then (the
+  // segments that the chains close take its first GW entries)
+  static_assert(kOwnAcc || GW + kAccSlots <= kSlots, "chain sums beside the last segments");
+  __shared__ f64x4 s_acc[kOwnAcc ? kSegBlock : 1];
+  auto s_acc_at = [&](int t) -> f64x4& {
+    if constexpr (kOwnAcc) return s_acc[t];
+    else return reinterpret_cast<f64x4*>(&s_park[t / kWave][kSlots - kAccSlots][0])[t % kWave];
+  };
   __shared__ int32_t s_cc[G], s_ww[G];
   __shared__ uint32_t s_seg[G], s_flags[G];
   __shared__ uint32_t s_cnum[kHotSlots];
@@ -1003,7 +1021,6 @@ seg_rows_kernel(SegmentArgs a, const uint32_t* __restrict__ packed, const uint32
       last_open = nvalid == SPAN && (p0 + SPAN) < n && !(packed[p0 + SPAN] & kHead);
       if (last_open) {
         pass = in_first && first_open;
-        s_acc[threadIdx.x] = acc;
         if (gl == 0) {
           s_cc[grp] = cc;
           s_ww[grp] = ww;
@@ -1019,7 +1036,12 @@ seg_rows_kernel(SegmentArgs a, const uint32_t* __restrict__ packed, const uint32
       const uint64_t mc = kPark ? __ballot(last_closes) : 0ull;
       if (last_closes) park(mc, mean_of(acc, cc), seg + hb, cc, ww, cur_key);
       parked += __popcll(mc) / LPR;
+      if (!kOwnAcc) {
+        while (parked > 0) pop(parked < kPop ? parked : kPop);
+        first_parked = 0;
+      }
     }
+    if (last_open) s_acc_at(threadIdx.x) = acc;
     if (gl == 0) s_flags[grp] = (nvalid > 0 ? kValid : 0u) | (last_open ? kOpen : 0u) | (pass ? kPass : 0u);
     __syncthreads();
 
@@ -1030,7 +1052,7 @@ seg_rows_kernel(SegmentArgs a, const uint32_t* __restrict__ packed, const uint32
       int tcc = fcc, tww = fww;
       if (owner) {
         for (int gg = grp - 1; gg >= 0; --gg) {
-          tot += s_acc[gg * LPR + gl];
+          tot += s_acc_at(gg * LPR + gl);
           tcc += s_cc[gg];
           tww += s_ww[gg];
           if (!(s_flags[gg] & kPass)) {
@@ -1054,12 +1076,12 @@ seg_rows_kernel(SegmentArgs a, const uint32_t* __restrict__ packed, const uint32
       while (parked > 0) pop(parked < kPop ? parked : kPop);
     // the chain that runs into the next tile
     if (grp == G - 1 && (s_flags[G - 1] & kOpen)) {
-      f64x4 tot = s_acc[(G - 1) * LPR + gl];
+      f64x4 tot = s_acc_at((G - 1) * LPR + gl);
       int tcc = s_cc[G - 1], tww = s_ww[G - 1];
       int gg = G - 1;
       while (gg > 0 && (s_flags[gg] & kPass)) {
         --gg;
-        tot += s_acc[gg * LPR + gl];
+        tot += s_acc_at(gg * LPR + gl);
         tcc += s_cc[gg];
         tww += s_ww[gg];
       }
