@@ -23,6 +23,7 @@ from __future__ import annotations
 import argparse
 import hashlib
 import json
+import math
 import os
 import platform
 import sys
@@ -277,11 +278,12 @@ def run_workload(name, args, torch, gba_step_mod, sdev, gba):
     # bytes and time over its launches, which split the work evenly but for
     # the last).
     S = 1 if w.optimizer == "adagrad" else 2
-    # vectors per thread of the dense kernel: 16 unless P is too small for
-    # 16 to give every compute unit a block step (4, else 1)
+    # vectors per thread of the dense kernel: the launcher's rule (dense_vecs
+    # in csrc/dense.hip), the count whose steps fill the chip best
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     nvec = w.P // 4
-    vecs = 16 if -(-nvec // (512 * 16)) >= cus else (4 if -(-nvec // (512 * 4)) >= cus else 1)
+    vecs = min((4, 3, 2, 1) if nvec < 512 * 4 * cus else (16, 14, 12, 10, 6, 4),
+               key=lambda v: (math.ceil(math.ceil(nvec / (512 * v)) / cus) * v, -v))
     if args.separate_dense:
         dense_call_bytes = K_eff * w.P * 4 + w.P * 4
         call_ms = breakdown["aggregate_dense"]
