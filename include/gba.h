@@ -18,6 +18,9 @@
  *    returns without synchronising.
  *  - Misuse the host can see (null pointer, bad size, unsupported width,
  *    workspace too small) returns a non-zero gba_status and enqueues nothing.
+ *  - A workspace size query never falls as N (n) grows, the other arguments
+ *    being the same: scratch sized for the largest input serves every smaller
+ *    one.
  *  - Errors that depend on device data are OR-ed into the caller's `*err`
  *    word as GBA_DERR_* bits; the library never clears it.  When `*err` is
  *    non-zero after the stream has drained, the outputs of that call are

@@ -1,5 +1,6 @@
 // C ABI of the GBA push-step (declared in include/gba.h): argument checks,
 // workspace layout and launch order.  No allocation, no synchronisation.
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <mutex>
@@ -20,7 +21,9 @@ bool width_ok(int32_t D) { return D >= 4 && D <= GBA_MAX_D && D % 4 == 0; }
 size_t sparse_bytes(int64_t N, int32_t D, int64_t R, int32_t sort_plan, SortPlan* plan_out) {
   const SortPlan plan = plan_sort(N, R, sort_plan);
   if (plan_out) *plan_out = plan;
-  return align_up(plan.bytes) + align_up(segments_workspace_bytes(N, D));
+  // the small sort's counts reach into the segments' scratch: nothing reads
+  // them after the sort
+  return std::max(align_up(plan.bytes), align_up(plan.keep_bytes) + align_up(segments_workspace_bytes(N, D)));
 }
 
 bool adam_args_ok(double beta1, double beta2, int64_t t) {
@@ -270,7 +273,7 @@ static gba_status sparse_call(const int64_t* ids, const float* rows, const int64
   a.num_unique = num_unique;
   a.err = err;
   if (ap) a.ap = *ap;
-  return from_hip(launch_segments(a, ws + align_up(plan.bytes), stream));
+  return from_hip(launch_segments(a, ws + align_up(plan.keep_bytes), stream));
 }
 
 gba_status gba_aggregate_sparse_plan(const int64_t* ids, const float* rows, const int64_t* contrib_offsets,

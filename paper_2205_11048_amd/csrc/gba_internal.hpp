@@ -68,6 +68,8 @@ struct SortPlan {
   int hot_cap;           // most hot IDs (hot plan)
   int64_t blocks;        // tiles of the first pass (the most of any pass)
   size_t bytes;          // workspace bytes
+  size_t keep_bytes;     // the first of them, with the sort's output and idle_out: past these the scratch is free
+                         // once the sort is done
 };
 // hot_mode: -1 picks the hot-key plan for large inputs whose key width leaves
 // room for it, 0 never, 1 whenever the key width allows.
@@ -87,7 +89,9 @@ struct SortHot {
 };
 // The plain plan below kSmallSortBelow keys (sort_small.hip).
 constexpr int64_t kSmallSortBelow = int64_t(1) << 22;
-size_t small_sort_bytes(int64_t n, int key_bits);
+// Room for the counts of every size up to n, at any key width: a workspace
+// queried for n holds every smaller input.
+size_t small_sort_count_room(int64_t n);
 hipError_t launch_small_sort(const int64_t* ids, int64_t n, int64_t R, int key_bits, void* ws, const uint32_t** keys_out,
                              const uint32_t** vals_out, uint32_t** idle_out, int32_t* err, hipStream_t stream);
 
@@ -138,6 +142,7 @@ struct SegmentArgs {
   SortHot hot;
   RowApply ap;            // mode 0: agg is written and no row is applied
 };
+// (the most of any size up to N, as for the sort)
 size_t segments_workspace_bytes(int64_t N, int32_t D);
 hipError_t launch_segments(const SegmentArgs& a, void* ws, hipStream_t stream);
 

@@ -5,6 +5,8 @@
 // its ID's run (the inverse map), and one row per distinct ID is gathered.  The
 // worker expands rows[inverse[i]] locally, so a Zipf-skewed request moves
 // U rows instead of n.
+#include <algorithm>
+
 #include "gba_device.hpp"
 #include "gba_internal.hpp"
 #include "run_heads.hpp"
@@ -27,7 +29,8 @@ static PullLayout pull_layout(int64_t n) {
   const size_t tiles = (size_t)(n > 0 ? ceil_div(n, kRunTile) : 1);
   size_t o = 0;
   L.off_tile = o;  o += align_up(tiles * 4);
-  L.off_group = o; o += align_up((size_t)run_groups(n) * 4);
+  // (the groups grow fourfold at 4096 tiles: their counts keep the room of the smaller sizes)
+  L.off_group = o; o += align_up((size_t)std::max(run_groups(n), std::min<int64_t>((int64_t)tiles / 4, 1024)) * 4);
   L.bytes = o;
   return L;
 }

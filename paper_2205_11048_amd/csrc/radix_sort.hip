@@ -24,6 +24,8 @@
 // passes sort only the cold keys, and the last one leaves a gap for the hot
 // runs below each key.  The result is the same stable sort, element for
 // element; which IDs are hot changes only the time it takes.
+#include <algorithm>
+
 #include "gba_device.hpp"
 #include "gba_internal.hpp"
 #include "sort_device.hpp"
@@ -878,12 +880,13 @@ SortPlan plan_sort(int64_t n, int64_t R, int hot_mode) {
     p.hot_cap = kRadix - cold_bins < kHotCap ? kRadix - cold_bins : kHotCap;
   }
   p.small = !hot && n < kSmallSortBelow;
-  if (p.small) {
-    p.bytes = small_sort_bytes(n, bits);
-    return p;
-  }
   p.blocks = n > 0 ? ceil_div(n, tile_keys<kItemsFirst>()) : 0;
-  p.bytes = sort_layout(n, p.blocks, p.hot).bytes;
+  const SortLayout L = sort_layout(n, p.blocks, p.hot);
+  p.bytes = p.keep_bytes = L.bytes;
+  // four arrays, then counts: here the small sort's may need more room, and get
+  // it for any smaller size and any key width, so that what the size query
+  // gave for n keys holds every smaller input too
+  if (!hot) p.bytes = std::max(p.bytes, L.off_hist + small_sort_count_room(std::min(n, kSmallSortBelow - 1)));
   return p;
 }
 

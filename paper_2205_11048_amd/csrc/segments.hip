@@ -28,6 +28,8 @@
 // only and write each segment at its place among all IDs; each hot ID is one
 // long segment, summed by hot_rows (per 4096-occurrence chunk, no per-position
 // segment logic) and finished by hot_finish, both in a fixed order.
+#include <algorithm>
+
 #include "gba_device.hpp"
 #include "gba_internal.hpp"
 #include "optim.hpp"
@@ -48,6 +50,9 @@ constexpr int kBatch = 8;                                    // positions per ba
 // SIMD) instead of 139 (3): more waves in flight beat more loads per wave.
 constexpr int kBatchPart = 4;
 constexpr int64_t kFineSpanBelow = int64_t(1) << 18;         // positions below which a lane group's span may be 16 or 8
+constexpr int64_t kSpanWork = int64_t(1024) * kWave * 32;    // positions * lanes per row of 1024 waves with spans of 32
+constexpr int64_t kSpan64From = int64_t(1) << 23;
+constexpr int64_t kSpan128From = int64_t(1) << 25;
 constexpr int kMaxBuckets = 1024;                            // contribution lookup buckets (most)
 
 // packed word of a sorted position
@@ -74,11 +79,10 @@ static int lanes_per_row(int D) {
 // wave: 16 or 8 then (20,480 positions at D = 16: 40 blocks instead of 10,
 // 13.8 us instead of 22).
 static int rows_span(int64_t N, int lpr) {
-  if (N >= (int64_t(1) << 25)) return 128;
-  if (N >= (int64_t(1) << 23)) return 64;
+  if (N >= kSpan128From) return 128;
+  if (N >= kSpan64From) return 64;
   if (N >= kFineSpanBelow) return 32;
-  const int64_t waves = N * lpr / ((int64_t)kWave * 32);   // of a pass with spans of 32
-  return waves >= 2048 ? 32 : (waves >= 1024 ? 16 : 8);
+  return N * lpr >= 2 * kSpanWork ? 32 : (N * lpr >= kSpanWork ? 16 : 8);
 }
 // The same for the hot IDs' pass: 32 below 2^25 occurrences, where chunks of
 // 128 per group leave less than a round of blocks for the chip (the pass and
@@ -86,7 +90,7 @@ static int rows_span(int64_t N, int lpr) {
 // 88 + 11 with 32; 10 M at D = 16 170 + 8, 164 + 9, 154 + 11).  Above, 64 takes
 // from the pass what the joining of twice the chunks costs (783 + 20, 770 +
 // 32).  Below the sizes that choose hot IDs by themselves 128 keeps the scratch small.
-static int hot_span(int64_t N) { return N >= (int64_t(1) << 25) || N < kSmallSortBelow ? kGroupSpan : 32; }
+static int hot_span(int64_t N) { return N >= kSpan128From || N < kSmallSortBelow ? kGroupSpan : 32; }
 // The segment count is kept at the start of every group.
 static int base_shift(int span) { return span >= 32 ? 5 : (span == 16 ? 4 : 3); }
 static_assert(kBaseSpan == 1 << 5, "base_shift");
@@ -160,7 +164,16 @@ static SegLayout seg_layout(int64_t N, int32_t D) {
   return L;
 }
 
-size_t segments_workspace_bytes(int64_t N, int32_t D) { return seg_layout(N, D).bytes; }
+// Where a lane group's span grows with N, the partial sums of the tiles
+// shrink: the most of any size up to N, so that a workspace for N positions
+// holds every smaller input too.
+size_t segments_workspace_bytes(int64_t N, int32_t D) {
+  const int lpr = lanes_per_row(D);
+  size_t most = seg_layout(N, D).bytes;
+  for (const int64_t from : {kSpanWork / lpr, 2 * kSpanWork / lpr, kFineSpanBelow, kSpan64From, kSpan128From})
+    if (from <= N) most = std::max(most, seg_layout(from - 1, D).bytes);
+  return most;
+}
 
 // ------------------------------------------------------------------ helpers
 // First index in [lo, hi) whose offset exceeds j, or hi (off non-decreasing).

@@ -14,6 +14,8 @@
 // 18.6 us (34 with three launches per byte), 26,624 24-bit keys 27.5 (41),
 // 256,000 27-bit keys 47 (53, and four launches more between), 300,007 21-bit
 // keys 37 (42), 851,968 24-bit keys 50 (56).
+#include <algorithm>
+
 #include "gba_device.hpp"
 #include "gba_internal.hpp"
 #include "sort_device.hpp"
@@ -464,10 +466,14 @@ struct SmallPlan {
   int64_t tiles, chunks;
 };
 
+constexpr int64_t kDigit11Below = int64_t(1) << 19;
+constexpr int64_t kDigit10Below = int64_t(1) << 20;
+static int widest_digit(int64_t n) { return n < kDigit11Below ? 11 : (n < kDigit10Below ? 10 : 9); }
+
 static SmallPlan small_plan(int64_t n, int key_bits) {
   SmallPlan p{};
   p.self = n <= kSelfMost;
-  const int most = n < (int64_t(1) << 19) ? 11 : (n < (int64_t(1) << 20) ? 10 : 9);
+  const int most = widest_digit(n);
   p.passes = (key_bits + most - 1) / most;
   // the narrowest digits first, as the first pass reads the widest keys
   int at = 0, widest = 8;
@@ -504,7 +510,20 @@ static SmallLayout small_layout(int64_t n, const SmallPlan& p) {
   return L;
 }
 
-size_t small_sort_bytes(int64_t n, int key_bits) { return small_layout(n, small_plan(n, key_bits)).bytes; }
+// Every size takes the most at the widest digits its size allows; the counts
+// shrink where these, or the tiles, change.
+size_t small_sort_count_room(int64_t n) {
+  auto counts = [](int64_t m) {
+    SmallPlan p = small_plan(m, 1);
+    p.bins_log2 = widest_digit(m);
+    const SmallLayout L = small_layout(m, p);
+    return L.bytes - L.off_hist;
+  };
+  size_t most = counts(n);
+  for (const int64_t end : {kDigit11Below - 1, kDigit10Below - 1, int64_t(512) * kMidBlock * 16})
+    if (end < n) most = std::max(most, counts(end));
+  return most;
+}
 
 hipError_t launch_small_sort(const int64_t* ids, int64_t n, int64_t R, int key_bits, void* ws, const uint32_t** keys_out,
                              const uint32_t** vals_out, uint32_t** idle_out, int32_t* err, hipStream_t stream) {
