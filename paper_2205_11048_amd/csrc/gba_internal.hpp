@@ -64,7 +64,7 @@ struct SortPlan {
   int passes;
   int first_bits;        // cold digit bits of the first pass (the later passes take 8)
   bool hot;              // hot-key plan: frequent IDs placed by the first pass
-  bool small;            // the small sort (plain plan below 2^22 keys)
+  bool small;            // the small sort (sort_small.hip)
   int hot_cap;           // most hot IDs (hot plan)
   int64_t blocks;        // tiles of the first pass (the most of any pass)
   size_t bytes;          // workspace bytes
@@ -87,8 +87,11 @@ struct SortHot {
   const uint32_t* meta = nullptr;       // [0] = H
   int bshift = 0;
 };
-// The plain plan below kSmallSortBelow keys (sort_small.hip).
+constexpr int64_t kHotPlanFrom = int64_t(1) << 22;   // keys from which hot IDs are chosen unasked
+// The small sort (sort_small.hip): which inputs of the plain plan it takes (all
+// of them below kSmallSortBelow keys).
 constexpr int64_t kSmallSortBelow = int64_t(1) << 22;
+bool small_sort_takes(int64_t n, int key_bits);
 // Room for the counts of every size up to n, at any key width: a workspace
 // queried for n holds every smaller input.
 size_t small_sort_count_room(int64_t n);

@@ -9,7 +9,7 @@
 // digit; and a scatter in which each tile adds up its own offsets (digit
 // start + chunk prefix + the tiles before it in its chunk), ranks its keys
 // stably in LDS and writes runs of equal digits together.
-// (The plain plan below 2^22 keys is in sort_small.hip.)
+// (Inputs of the plain plan below 2^20 keys, some to 2^22, are in sort_small.hip.)
 // Ranks inside a wave come from ballots that match lanes holding the same
 // digit, so skewed (Zipf) keys cost no LDS atomics on hot bins in the scatter.
 //
@@ -57,8 +57,6 @@ constexpr int kHotBlock = 1024;
 constexpr int kHotCap = 254;           // most hot IDs (one bin each; the lookup reads one entry past H)
 constexpr int kHotBuckets = 1024;      // lookup buckets over the top 10 key bits
 constexpr uint32_t kHotMinCount = 4;   // a sampled ID must occur this often to be hot
-constexpr int64_t kHotMinKeys = int64_t(1) << 22;   // below this the plain sort is used
-static_assert(kHotMinKeys == kSmallSortBelow, "the plain plan below the hot plan's sizes is the small sort");
 
 // Pass kinds.
 enum : int {
@@ -871,7 +869,7 @@ SortPlan plan_sort(int64_t n, int64_t R, int hot_mode) {
     hot = hot && p.passes >= 3;
   }
   if (hot_mode == 0) hot = false;
-  if (hot_mode < 0) hot = hot && n >= kHotMinKeys;
+  if (hot_mode < 0) hot = hot && n >= kHotPlanFrom;
   p.hot = hot;
   if (hot) {
     p.passes = hot_passes;
@@ -879,7 +877,7 @@ SortPlan plan_sort(int64_t n, int64_t R, int hot_mode) {
     const int cold_bins = 1 << hot_first;
     p.hot_cap = kRadix - cold_bins < kHotCap ? kRadix - cold_bins : kHotCap;
   }
-  p.small = !hot && n < kSmallSortBelow;
+  p.small = !hot && small_sort_takes(n, bits);
   p.blocks = n > 0 ? ceil_div(n, tile_keys<kItemsFirst>()) : 0;
   const SortLayout L = sort_layout(n, p.blocks, p.hot);
   p.bytes = p.keep_bytes = L.bytes;

@@ -90,7 +90,7 @@ static int rows_span(int64_t N, int lpr) {
 // 88 + 11 with 32; 10 M at D = 16 170 + 8, 164 + 9, 154 + 11).  Above, 64 takes
 // from the pass what the joining of twice the chunks costs (783 + 20, 770 +
 // 32).  Below the sizes that choose hot IDs by themselves 128 keeps the scratch small.
-static int hot_span(int64_t N) { return N >= kSpan128From || N < kSmallSortBelow ? kGroupSpan : 32; }
+static int hot_span(int64_t N) { return N >= kSpan128From || N < kHotPlanFrom ? kGroupSpan : 32; }
 // The segment count is kept at the start of every group.
 static int base_shift(int span) { return span >= 32 ? 5 : (span == 16 ? 4 : 3); }
 static_assert(kBaseSpan == 1 << 5, "base_shift");

@@ -1,15 +1,16 @@
-// The ID sort below 2^22 keys without hot keys: stable LSD radix passes as in
+// The ID sort of small inputs without hot keys: stable LSD radix passes as in
 // the large sort, but with as few launches as the size allows, since a launch
 // costs 4 to 5 us on a busy stream however few keys it moves.
-//  * Digits of up to 11 bits (10 from 2^19 keys, 9 from 2^20, where the rows
-//    of counts would outgrow the workspace): two passes for 17- to 22-bit
-//    keys, three to 33 bits, instead of one per byte.
+//  * Digits of up to 11 bits where a wider digit saves a pass that costs more
+//    (pass_bits).
 //  * Up to kSelfMost keys, one launch per pass: every block counts the digits
 //    of all keys itself (before and after its own tile), so no launch has to
 //    count for it.
 //  * Above, two launches per pass: the counts per tile and per chunk of
 //    tiles, and a scatter whose blocks add up the chunk rows (128 at most)
-//    themselves instead of reading them scanned by a launch in between.
+//    themselves instead of reading them scanned by a launch in between.  That
+//    costs every block, so from 2^20 keys the large sort's three launches per
+//    pass are as fast or faster (small_sort_takes).
 // Bound by the launches' latency, not by bytes.  Measured: 20,480 17-bit keys
 // 18.6 us (34 with three launches per byte), 26,624 24-bit keys 27.5 (41),
 // 256,000 27-bit keys 47 (53, and four launches more between), 300,007 21-bit
@@ -468,13 +469,48 @@ struct SmallPlan {
 
 constexpr int64_t kDigit11Below = int64_t(1) << 19;
 constexpr int64_t kDigit10Below = int64_t(1) << 20;
+constexpr int64_t kFourTileChunks = 512;   // most tiles of a pass with chunks of four, not eight
+
+// Bits of the widest digit of a key of key_bits: as few passes as digits of 9
+// bits allow, or wider ones where the pass they save costs more than they do.
+// us per pass, digits of 8, 9, 10 and 11 bits: 130,000 keys 11.7 12.3 14.1 16.1,
+// 260,000 12.4 13.3 16.4 18.8, 400,000 13.1 15.3 20.5 23.3, 850,000 18.2 22.3
+// 31.8 -: two passes of 11 bits instead of three of 8 pay to about 200,000 keys
+// (22-bit keys, 130,000: 32 us and 35, 400,000: 47 and 39), two of 10 to about
+// 330,000, three of 10 instead of four of 8 to about 200,000, three of 11 as
+// long as a pass is one launch (32-bit keys, 20,000: 36 us and 37, 65,000: 46
+// and 44); one pass of either pays as far as its counts fit.
+static int pass_bits(int64_t n, int key_bits) {
+  for (int passes = 1;; ++passes) {
+    const int bits = (key_bits + passes - 1) / passes;
+    if (bits <= 9) return bits;
+    if (bits == 10 && n < (passes == 1 ? kDigit10Below : (passes == 2 ? 5 << 16 : 3 << 16))) return bits;
+    if (bits == 11 && n < (passes == 1 ? kDigit11Below : (passes == 2 ? 3 << 16 : kSelfMost + 1))) return bits;
+  }
+}
+
+// From 2^20 keys the chunk rows that every scatter block adds up cost what the
+// scan between them would (850,000 24-bit keys 54.6 us, 55.3 with the large
+// sort; 1.7 M 76 and 71, 3.3 M 109 and 92): the large sort then, but for keys
+// that 9-bit digits take in a pass less, and for these as far as that pass
+// pays: one pass to 2^22 keys (9-bit keys, 3.3 M: 51 us and 60), two to 3 * 2^20
+// (18-bit, 2.6 M: 72 and 80, 3.3 M: 89 and 88), three to 2^21 (27-bit, 1.7 M: 85
+// and 93, 2.1 M: 95 and 93).
+bool small_sort_takes(int64_t n, int key_bits) {
+  if (n < kDigit10Below) return true;
+  const int passes = (key_bits + 8) / 9;
+  return passes < (key_bits + 7) / 8 && n < (int64_t)(5 - passes) << 20;
+}
+static_assert(kSmallSortBelow == int64_t(4) << 20, "one pass");
+
+// The widest digit of any key for n keys.
 static int widest_digit(int64_t n) { return n < kDigit11Below ? 11 : (n < kDigit10Below ? 10 : 9); }
 
 static SmallPlan small_plan(int64_t n, int key_bits) {
   SmallPlan p{};
   p.self = n <= kSelfMost;
-  const int most = widest_digit(n);
-  p.passes = (key_bits + most - 1) / most;
+  const int bits = pass_bits(n, key_bits);
+  p.passes = (key_bits + bits - 1) / bits;
   // the narrowest digits first, as the first pass reads the widest keys
   int at = 0, widest = 8;
   for (int k = 0; k < p.passes; ++k) {
@@ -485,9 +521,9 @@ static SmallPlan small_plan(int64_t n, int key_bits) {
   }
   p.bins_log2 = widest;   // the rows' width: 256 counters at least
   // 2048-key tiles below 2^20 keys (blocks for every compute unit), 4096 above (longer runs)
-  p.items = n < (int64_t(1) << 20) ? 8 : 16;
+  p.items = n < kDigit10Below ? 8 : 16;
   p.tiles = ceil_div(n > 0 ? n : 1, (int64_t)kMidBlock * p.items);
-  p.chunk_shift = p.tiles <= 512 ? 2 : 3;   // at most 128 chunk rows for a scatter block to add up
+  p.chunk_shift = p.tiles <= kFourTileChunks ? 2 : 3;   // at most 128 chunk rows for a scatter block to add up
   p.chunks = ceil_div(p.tiles, int64_t(1) << p.chunk_shift);
   return p;
 }
@@ -520,7 +556,7 @@ size_t small_sort_count_room(int64_t n) {
     return L.bytes - L.off_hist;
   };
   size_t most = counts(n);
-  for (const int64_t end : {kDigit11Below - 1, kDigit10Below - 1, int64_t(512) * kMidBlock * 16})
+  for (const int64_t end : {kDigit11Below - 1, kDigit10Below - 1, kFourTileChunks * kMidBlock * 16})
     if (end < n) most = std::max(most, counts(end));
   return most;
 }
@@ -574,24 +610,18 @@ hipError_t launch_small_sort(const int64_t* ids, int64_t n, int64_t R, int key_b
 #define GBA_MID_HIST(F, IT, B, T)                                                                                  \
   hipLaunchKernelGGL((mid_hist_kernel<F, IT, B, T>), hgrid, hblock, 0, stream, kin, n, shift, mask, R, hist, chunk, \
                      p.tiles, err)
-    // more than 512 tiles: 4096 keys each, from 2^21 keys
-#define GBA_MID_HIST_BITS(F)                                       \
-  if (p.items == 16) {                                             \
-    if (p.bins_log2 == 8) {                                        \
-      if (p.chunk_shift == 2) GBA_MID_HIST(F, 16, 8, 4);           \
-      else GBA_MID_HIST(F, 16, 8, 8);                              \
-    } else {                                                       \
-      if (p.chunk_shift == 2) GBA_MID_HIST(F, 16, 9, 4);           \
-      else GBA_MID_HIST(F, 16, 9, 8);                              \
-    }                                                              \
-  } else if (p.bins_log2 == 8) {                                   \
-    GBA_MID_HIST(F, 8, 8, 4);                                      \
-  } else if (p.bins_log2 == 9) {                                   \
-    GBA_MID_HIST(F, 8, 9, 4);                                      \
-  } else if (p.bins_log2 == 10) {                                  \
-    GBA_MID_HIST(F, 8, 10, 4);                                     \
-  } else {                                                         \
-    GBA_MID_HIST(F, 8, 11, 4);                                     \
+    // (from 2^20 keys small_sort_takes leaves keys with a 9-bit digit only)
+#define GBA_MID_HIST_BITS(F)                             \
+  if (p.items == 16) {                                   \
+    if (p.chunk_shift == 2) GBA_MID_HIST(F, 16, 9, 4);   \
+    else GBA_MID_HIST(F, 16, 9, 8);                      \
+  } else {                                               \
+    switch (p.bins_log2) {                               \
+      case 8: GBA_MID_HIST(F, 8, 8, 4); break;           \
+      case 9: GBA_MID_HIST(F, 8, 9, 4); break;           \
+      case 10: GBA_MID_HIST(F, 8, 10, 4); break;         \
+      default: GBA_MID_HIST(F, 8, 11, 4); break;         \
+    }                                                    \
   }
     if (pass == 0) {
       GBA_MID_HIST_BITS(true)
@@ -613,8 +643,7 @@ hipError_t launch_small_sort(const int64_t* ids, int64_t n, int64_t R, int key_b
       default: GBA_MID(F, 8, 11); break;         \
     }                                            \
   } else {                                       \
-    if (p.bins_log2 == 8) GBA_MID(F, 16, 8);     \
-    else GBA_MID(F, 16, 9);                      \
+    GBA_MID(F, 16, 9);                           \
   }
     if (pass == 0) {
       GBA_MID_BITS(true)

@@ -1,7 +1,8 @@
-"""The ID sort below 2^22 keys at the edges of its rules: one launch per pass
-up to 32,768 keys, digits of 11, 10 and 9 bits below 2^19 keys, below 2^20 and
-above, tiles of 2048 and 4096 keys, chunks of 4 and 8 tiles; against a stable
-sort, which the outputs equal element for element."""
+"""The plain ID sort at the edges of its rules: one launch per pass up to
+32,768 keys, two below 2^20 (2^21 to 2^22 for keys that 9-bit digits take in a
+pass less), three above, the sizes up to which digits of 10 and 11 bits save a
+pass, tiles of 2048 and 4096 keys; against a stable sort, which the outputs
+equal element for element."""
 import pytest
 import torch
 
@@ -43,6 +44,18 @@ def test_sort_key_widths(n, R):
 @pytest.mark.parametrize("n", [(1 << 19) - 1, 1 << 19, (1 << 20) - 1, 1 << 20, (1 << 21) + 1, (1 << 22) - 1])
 def test_sort_digit_and_tile_rules(n, R):
     ids = _ids(n, R, n % 1013, 3.0)
+    keys, index, err = _sort(ids, R)
+    ref, ref_index = torch.sort(ids, stable=True)
+    assert err == 0
+    assert torch.equal(keys, ref) and torch.equal(index, ref_index)
+
+
+@pytest.mark.parametrize("bits", [9, 10, 11, 17, 18, 20, 22, 25, 27, 30, 32])
+@pytest.mark.parametrize("n", [(3 << 16) - 1, 3 << 16, (5 << 16) - 1, 5 << 16, (1 << 20) + 1, (1 << 21) - 1, 1 << 21,
+                               (3 << 20) - 1, 3 << 20, (1 << 22) - 1])
+def test_sort_digit_lines(n, bits):
+    R = 1 << bits
+    ids = _ids(n, R, n % 1013 + bits, 3.0)
     keys, index, err = _sort(ids, R)
     ref, ref_index = torch.sort(ids, stable=True)
     assert err == 0
