@@ -53,6 +53,7 @@ constexpr int64_t kFineSpanBelow = int64_t(1) << 18;         // positions below 
 constexpr int64_t kSpanWork = int64_t(1024) * kWave * 32;    // positions * lanes per row of 1024 waves with spans of 32
 constexpr int64_t kSpan64From = int64_t(1) << 23;
 constexpr int64_t kSpan128From = int64_t(1) << 25;
+constexpr int64_t kHotWideFrom = int64_t(1) << 24;           // occurrences from which the hot IDs' spans double
 constexpr int kMaxBuckets = 1024;                            // contribution lookup buckets (most)
 
 // packed word of a sorted position
@@ -84,13 +85,25 @@ static int rows_span(int64_t N, int lpr) {
   if (N >= kFineSpanBelow) return 32;
   return N * lpr >= 2 * kSpanWork ? 32 : (N * lpr >= kSpanWork ? 16 : 8);
 }
-// The same for the hot IDs' pass: 32 below 2^25 occurrences, where chunks of
-// 128 per group leave less than a round of blocks for the chip (the pass and
-// its finish, us: 6.5 M occurrences at D = 32 125 + 7 with 128, 93 + 9 with 64,
-// 88 + 11 with 32; 10 M at D = 16 170 + 8, 164 + 9, 154 + 11).  Above, 64 takes
-// from the pass what the joining of twice the chunks costs (783 + 20, 770 +
-// 32).  Below the sizes that choose hot IDs by themselves 128 keeps the scratch small.
-static int hot_span(int64_t N) { return N >= kSpan128From || N < kHotPlanFrom ? kGroupSpan : 32; }
+// The same for the hot IDs' pass, whose blocks each sum one chunk (a tile of
+// this span) and leave it to hot_finish, one block per ID, to join an ID's
+// chunks.  Below 2^25 occurrences chunks of 128 per group would leave less
+// than a round of blocks for the chip, but wide rows have few groups per
+// block: chunks below some 1000 occurrences cost more in the joining than they
+// give the pass.  So 32 per group up to 8 lanes per row, 64 with 16 and 128 with
+// more, and twice that from 2^24 with 8 lanes or more.  The means of two skews
+// with 32 / 64 / 128 per group, us: D = 16, 4.3 M 283 292 321 and 266 267 323; D
+// = 32, 4.3 M 319 319 346 and 308 323 347, 20 M 874 862 872 and 786 759 786; D =
+// 64, 6.5 M 564 548 564 and 535 501 523, 20 M 1374 1310 1298 and 1245 1128 1117;
+// D = 128, 4.3 M 707 657 639 and 710 617 607; D = 256, 4.3 M 1392 1179 1082 and
+// 1546 1181 1021.  From 2^25 half of 128 takes from the pass what the joining of
+// twice the chunks costs (D = 32, 65.5 M: pass and joining 783 + 20, 770 + 32).
+// Below the sizes that choose hot IDs by themselves 128 keeps the scratch small.
+static int hot_span(int64_t N, int lpr) {
+  if (N >= kSpan128From || N < kHotPlanFrom) return kGroupSpan;
+  const int span = lpr <= 8 ? 32 : (lpr == 16 ? 64 : 128);
+  return N >= kHotWideFrom && lpr >= 8 ? std::min(2 * span, kGroupSpan) : span;
+}
 // The segment count is kept at the start of every group.
 static int base_shift(int span) { return span >= 32 ? 5 : (span == 16 ? 4 : 3); }
 static_assert(kBaseSpan == 1 << 5, "base_shift");
@@ -153,7 +166,7 @@ static SegLayout seg_layout(int64_t N, int32_t D) {
   // the cold positions below it
   L.off_cnum = o;      o += align_up(3 * (kHotSlots + 1) * 4);
   // per chunk of a hot run: float64 sums and (contributions, active, first and last contribution)
-  L.hot_span = hot_span(N);
+  L.hot_span = hot_span(N, lpr);
   L.hot_chunks = (N > 0 ? ceil_div(N, rows_tile(lpr, L.hot_span)) : 1) + kHotSlots;
   // (the run-head groups' counts lie here too: they are last read by the
   // position pass, before the hot sums are written; hot_chunks * D * 8 is at
@@ -170,7 +183,7 @@ static SegLayout seg_layout(int64_t N, int32_t D) {
 size_t segments_workspace_bytes(int64_t N, int32_t D) {
   const int lpr = lanes_per_row(D);
   size_t most = seg_layout(N, D).bytes;
-  for (const int64_t from : {kSpanWork / lpr, 2 * kSpanWork / lpr, kFineSpanBelow, kSpan64From, kSpan128From})
+  for (const int64_t from : {kSpanWork / lpr, 2 * kSpanWork / lpr, kFineSpanBelow, kSpan64From, kHotWideFrom, kSpan128From})
     if (from <= N) most = std::max(most, seg_layout(from - 1, D).bytes);
   return most;
 }
