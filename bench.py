@@ -23,7 +23,6 @@ from __future__ import annotations
 import argparse
 import hashlib
 import json
-import math
 import os
 import platform
 import sys
@@ -91,13 +90,16 @@ def kernel_source_sha(path):
 
 def measured_traffic(kernel, workload_name):
     """HBM bytes per launch from committed rocprofv3 counter runs, if they
-    were taken on the current source of the kernel; else None."""
+    were taken on the current source of the kernel; else None.  A kernel named
+    without its last template arguments (the launch rule's choice) stands for
+    whichever variant was measured on the workload."""
     p = os.path.join(ROOT, "profiles", "traffic.json")
     if not os.path.exists(p):
         return None
     with open(p) as f:
         data = json.load(f)
-    e = data.get(f"{kernel}@{workload_name}")
+    e = next((v for k, v in data.items() if k.endswith(f"@{workload_name}") and
+              (k.startswith(kernel + "@") or k.startswith(kernel[:-1] + ", "))), None)
     if not e or e.get("source_sha256_16") != kernel_source_sha(e["source"]):
         return None
     return e["bytes_per_launch"]
@@ -278,21 +280,15 @@ def run_workload(name, args, torch, gba_step_mod, sdev, gba):
     # bytes and time over its launches, which split the work evenly but for
     # the last).
     S = 1 if w.optimizer == "adagrad" else 2
-    # vectors per thread of the dense kernel: the launcher's rule (dense_vecs
-    # in csrc/dense.hip), the count whose steps fill the chip best
-    cus = torch.cuda.get_device_properties(0).multi_processor_count
-    nvec = w.P // 4
-    vecs = min((4, 3, 2, 1) if nvec < 512 * 4 * cus else (16, 14, 12, 10, 6, 4),
-               key=lambda v: (math.ceil(math.ceil(nvec / (512 * v)) / cus) * v, -v))
     if args.separate_dense:
         dense_call_bytes = K_eff * w.P * 4 + w.P * 4
         call_ms = breakdown["aggregate_dense"]
-        kname = f"aggregate_dense_kernel<0, false, {vecs}>"
+        kname = "aggregate_dense_kernel<0, false>"
         launches = gba.gba_aggregate_dense_launches(w.P, w.K, gba.DENSE_SUM)
     else:
         dense_call_bytes = K_eff * w.P * 4 + (2 + 2 * S) * w.P * 4
         call_ms = breakdown["aggregate_apply_dense"]
-        kname = f"aggregate_dense_kernel<{S}, false, {vecs}>"
+        kname = f"aggregate_dense_kernel<{S}, false>"
         launches = gba.gba_aggregate_dense_launches(w.P, w.K, gba.DENSE_ADAGRAD if S == 1 else gba.DENSE_ADAM)
     dense_kernel_bytes = dense_call_bytes / launches
     dk_ms = call_ms / launches

@@ -3,15 +3,16 @@
 // (Adagrad, Adam; Table 1 names them), separately or fused.
 //
 // The reduction streams K_eff * P floats from HBM.  A block of 8 waves owns
-// 128 KB of the output at a time; each wave reads 16 KB of one gradient as 16
-// consecutive 1 KB loads before moving to the next gradient, so the memory
-// system sees long contiguous runs per gradient wherever the caller placed
-// the K buffers (short runs from many buffers at once were measured to lose
-// up to 15% of bandwidth to DRAM row conflicts, depending on the buffers'
-// relative addresses).  Threads take fewer vectors than 16 where such blocks
-// would leave part of the chip idle at the end (dense_vecs).  Each thread
-// accumulates its vectors in float64 in buffer order, so the only rounding is
-// the final one to float.
+// 8 KB of the output per vector of its threads, 128 KB with 16; each wave reads
+// 1 KB per vector of one gradient in a row (16 KB) before moving to the next
+// gradient, so the memory system sees long contiguous runs per gradient
+// wherever the caller placed the K buffers (short runs from many buffers at
+// once were measured to lose up to 15% of bandwidth to DRAM row conflicts,
+// depending on the buffers' relative addresses).  Threads take fewer vectors
+// than 16 where such blocks would leave part of the chip idle at the end and
+// the shorter runs cost less than that (dense_vecs).  Each thread accumulates
+// its vectors in float64 in buffer order, so the only rounding is the final
+// one to float.
 #include <algorithm>
 
 #include "gba_device.hpp"
@@ -187,7 +188,7 @@ aggregate_dense_kernel(const float* const* __restrict__ grads, const float* __re
     const int64_t nvec = P / 4;
     for (int64_t s = step0 + blockIdx.x; s < step_end; s += gridDim.x) {
       const int64_t b0 = s * dense_span<VECS>();
-      // wave w covers vectors [b0 + w * 1024, +1024): lane l takes l, l + 64, ...
+      // wave w covers vectors [b0 + w * 64 VECS, +64 VECS): lane l takes l, l + 64, ...
       const int64_t vb = b0 + (int64_t)(threadIdx.x / kWave) * (kWave * VECS) + (threadIdx.x % kWave);
       f64x4 acc[VECS];
 #pragma unroll
@@ -261,34 +262,56 @@ static int device_cus() {
 }
 
 // Vectors per thread for P elements (f32x4; a wave reads that many KB of one
-// gradient in a row).  A compute unit takes one block step after another, so
-// the call lasts about ceil(steps / cus) steps of vecs: the choice is the vecs
-// that makes this least, the larger of two equal ones (longer runs), but never
-// 8, whose single step per compute unit keeps too few loads in flight where
-// two steps of 4 are the same work (P = 4 M, K = 32: 99 us against 92).  From
-// four vectors for every thread of the chip on, at least 4.  Measured, us with
-// 16 (4 or 1 where 16 left compute units without a step) against this rule,
-// Adagrad, K = 64 or 100: P = 2 M 95 and 83, 4.2 M 295 and 265, 6 M 397 and
-// 388, 8 M 532 and 520, 12 M 538 and 510, 20 M 882 and 810.
-static int dense_vecs(int64_t P, int cus) {
-  constexpr int kFew[] = {4, 3, 2, 1};
-  constexpr int kMany[] = {16, 14, 12, 10, 6, 4};
+// gradient in a row).  16 from where that gives every compute unit a block
+// step, 4 below, and 1 where 4 would not.  A compute unit takes one block step
+// after another, so the call lasts about ceil(steps / cus) steps of vecs: where
+// another count makes this less, the last steps fill the chip better.  But
+// with many gradients runs of 4 and 6 KB read 4 to 5 % slower, those of 10 to
+// 14 up to 3 %, and 8 is never as good (P = 4 M, K = 32: 99 us against 92).  So
+// (us without and with, Adagrad, K = 64 where no K is given)
+//  * 16 gives way to 14, 12 or 10, with few gradients also to 6 or 4, for more
+//    than a sixteenth (P = 8.5 M 495 and 360, 12 M 549 and 512, 27 M 1245 and
+//    1154, 36 M 1661 and 1538, 77 M with Adam, K = 4 661 and 609; a sixteenth
+//    or less is not worth it: 15 M, K = 16 205 and 211, 64 M 2813 and 2820, and
+//    2922 with runs of 4 KB); with the running sum for an eighth (36 M, K = 16
+//    501 and 488; a ninth: 52 M, K = 4 369 and 380);
+//  * 4 gives way to a larger count for more than an eighth (2.2 M 121 and 91,
+//    4.7 M 226 and 194), and where the steps are no more work and there are
+//    gradients enough for the longer runs to pay for the fewer blocks in flight
+//    (8 M, K = 4 49 and 53, K = 24 152 and 150, K = 128 692 and 649), or the
+//    running sum's 16 bytes per element (8 M, K = 4 50 and 47);
+//  * 1 gives way to 4, 3 or 2, never less work, where there are gradients
+//    enough, the fewer the longer the runs (1.2 M, K = 4 10.4 and 11.3, K = 24
+//    27.4 and 25.5, K = 128 118 and 95; 1.7 M, K = 10 21.8 and 20.5; with the
+//    running sum 1.2 M, K = 10 14.4 and 12.6), and to 2, a single step, only where
+//    most compute units have one (K = 37: 0.8 M 24.5 and 25.7, 1.05 M 30.3 and 29.4);
+//  * with no gradients (finishing a running sum) 1 has the most loads in
+//    flight (8 M 47.5 with 4, 51.3 with 16 and 41.3; 16 M 95.6 with 16 and 76.5).
+static int dense_vecs(int64_t P, int32_t K, bool carry, int cus) {
   const int64_t nvec = P / 4;
   if (cus <= 0) return 16;
-  int best = 0;
-  int64_t best_cost = 0;
+  if (K == 0) return 1;
+  auto steps = [&](int v) { return ceil_div(nvec, (int64_t)kSumBlock * v); };
+  auto cost = [&](int v) { return ceil_div(steps(v), cus) * v; };
+  const int base = steps(16) >= cus ? 16 : (steps(4) >= cus ? 4 : 1);
+  int best = base;   // the least cost, the larger of equal counts
   auto consider = [&](int v) {
-    const int64_t cost = ceil_div(ceil_div(nvec, (int64_t)kSumBlock * v), cus) * v;
-    if (best == 0 || cost < best_cost) {
-      best = v;
-      best_cost = cost;
-    }
+    if (best == base ? cost(v) <= cost(base) : cost(v) < cost(best)) best = v;
   };
-  if (nvec < dense_span<4>() * cus)
-    for (int v : kFew) consider(v);
-  else
-    for (int v : kMany) consider(v);
-  return best;
+  if (base == 16) {
+    for (int v : {14, 12, 10}) consider(v);
+    if (carry) return 8 * cost(best) <= 7 * cost(16) ? best : 16;
+    if (K <= 10)
+      for (int v : {6, 4}) consider(v);
+    return 16 * cost(best) < 15 * cost(16) ? best : 16;
+  }
+  if (base == 4) {
+    for (int v : {16, 14, 12, 10, 6}) consider(v);
+    return carry || K >= 24 || 8 * cost(best) < 7 * cost(4) ? best : 4;
+  }
+  for (int v : {4, 3, 2}) consider(v);
+  if (best == 2 && 20 * steps(2) < 17 * (int64_t)cus) return 1;
+  return K >= (carry ? (best == 2 ? 16 : 10) : 144 / (best * best)) ? best : 1;
 }
 
 template <int MODE, bool CARRY, int VECS>
@@ -316,7 +339,7 @@ static hipError_t launch_dense_mode(const float* const* grads, const float* w, i
                                     hipStream_t stream) {
   if (P <= 0) return hipSuccess;
   const int cus = device_cus();
-  switch (dense_vecs(P, cus)) {
+  switch (dense_vecs(P, K, CARRY, cus)) {
 #define GBA_DENSE_VECS(V) \
   case V: return launch_dense_vecs<MODE, CARRY, V>(grads, w, K, P, out, st, run, denom, reset, cus, stream);
     GBA_DENSE_VECS(1)
@@ -337,7 +360,7 @@ template <int MODE, bool CARRY>
 static int64_t launch_count(int64_t P, int32_t K) {
   const int cus = device_cus();
   int64_t steps = 0, round = 0;
-  switch (dense_vecs(P, cus)) {
+  switch (dense_vecs(P, K, CARRY, cus)) {
 #define GBA_DENSE_VECS(V) \
   case V: dense_rounds<MODE, CARRY, V>(P, K, cus, &steps, &round); break;
     GBA_DENSE_VECS(1)
