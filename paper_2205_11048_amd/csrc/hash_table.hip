@@ -88,10 +88,12 @@ hash_clear_kernel(int64_t* __restrict__ slot_ids, int32_t* __restrict__ slot_row
 
 // Among the active lanes, the first lane that holds this lane's value, looked
 // for among the first kLeaderRounds distinct values (past them a lane is its
-// own leader).  A frequent ID is nearly always among those.
+// own leader).  A frequent ID is nearly always among those.  *repeats, the same
+// in every lane, tells whether one of them was held twice.
 constexpr int kLeaderRounds = 16;
-__device__ __forceinline__ int wave_leader(int64_t v) {
+__device__ __forceinline__ int wave_leader(int64_t v, bool* repeats) {
   int lead = lane_id();
+  *repeats = false;
   uint64_t todo = __ballot(true);
   for (int r = 0; r < kLeaderRounds && todo; ++r) {
     const int l = (int)__ffsll((unsigned long long)todo) - 1;
@@ -99,7 +101,9 @@ __device__ __forceinline__ int wave_leader(int64_t v) {
                           (uint32_t)__builtin_amdgcn_readlane((int)v, l);
     const bool same = v == first;
     if (same) lead = l;
-    todo &= ~__ballot(same);
+    const uint64_t lanes = __ballot(same);
+    *repeats |= (lanes & (lanes - 1)) != 0ull;
+    todo &= ~lanes;
   }
   return lead;
 }
@@ -112,7 +116,9 @@ __device__ __forceinline__ int wave_leader(int64_t v) {
 // hold the ID, and reads the slot past the caches before it swaps (1 M
 // positions, 93,000 of the most frequent ID, on an empty index: 700 -> 260 us
 // with the clearing; 6.5 M 993 -> 540; 30 M 2230 -> 1675; known IDs are found
-// without either).
+// without either).  A wave that sees no ID twice swaps at once: where all IDs
+// differ the reads only cost (this one and the row's: 1 M positions 180 us and,
+// without, 166, 10 M 1631 and 1468).
 template <bool SHARED>
 __device__ __forceinline__ int64_t claim_or_find(int64_t* slot_ids, int64_t mask, int64_t id, uint64_t h) {
   int64_t s = (int64_t)(h & (uint64_t)mask);
@@ -122,10 +128,11 @@ __device__ __forceinline__ int64_t claim_or_find(int64_t* slot_ids, int64_t mask
     const int64_t cur = slot_ids[s];
     if (cur == id) return s;
     if (cur == GBA_EMPTY_ID) {
-      const int lead = SHARED ? wave_leader(id) : lane_id();
+      bool repeats = false;
+      const int lead = SHARED ? wave_leader(id, &repeats) : lane_id();
       int64_t prev = GBA_EMPTY_ID;
       if (lead == lane_id()) {
-        if (SHARED) prev = __hip_atomic_load(slot_ids + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (repeats) prev = __hip_atomic_load(slot_ids + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (prev == GBA_EMPTY_ID)
           prev = (int64_t)atomicCAS(reinterpret_cast<unsigned long long*>(slot_ids + s),
                                     (unsigned long long)GBA_EMPTY_ID, (unsigned long long)id);
@@ -173,9 +180,12 @@ hash_claim_kernel(int64_t* __restrict__ slot_ids, int32_t* __restrict__ slot_row
             // the slot has no row yet: exactly one position lists it (kNoRow
             // cannot turn into a row during this launch), and every position
             // of the slot reads its row after the rows are handed out
-            // (asked by one lane per slot of the wave, past the caches first)
-            if (r == kNoRow && wave_leader(s) == lane_id() &&
-                __hip_atomic_load(slot_rows + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == kNoRow)
+            // (asked by one lane per slot of the wave, past the caches first
+            // where a slot is asked for twice)
+            bool repeats = false;
+            if (r == kNoRow && wave_leader(s, &repeats) == lane_id() &&
+                (!repeats ||
+                 __hip_atomic_load(slot_rows + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == kNoRow))
               claimed = atomicCAS(slot_rows + s, kNoRow, kPendingRow) == kNoRow;
             waits = true;
           }
