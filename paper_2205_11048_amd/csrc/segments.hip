@@ -245,6 +245,15 @@ __device__ __forceinline__ int contribution_of(const int32_t* s_off, const int32
   return m < K ? m : K - 1;
 }
 
+// Row accesses through the caches or past them.
+template <bool CACHED>
+__device__ __forceinline__ f32x4 load_row(const f32x4* p) { return CACHED ? *p : load_stream(p); }
+template <bool CACHED>
+__device__ __forceinline__ void store_row(f32x4* p, f32x4 v) {
+  if (CACHED) *p = v;
+  else store_stream(p, v);
+}
+
 // The optimiser on one lane's 4 floats of a row (mode 1 Adagrad, 2 Adam), with
 // the row apply's arithmetic.
 __device__ __forceinline__ void update4(int mode, const OptF32& c, f32x4& pv, f32x4& s1, f32x4& s2, f32x4 g) {
@@ -749,7 +758,15 @@ seg_meta_kernel(SegmentArgs a, RunHeads heads, const int32_t* __restrict__ bucke
 // 183 + 22 for the pass, the row apply and the tags as launches of their own;
 // D = 16 with Adam 219 against 104 + 119, D = 64 with Adagrad 137 against 63 +
 // 74 (both storing the means too), so every width applies its rows here.
-template <int LPR, int APPLY>
+//
+// With a row apply, rows below 128 bytes that are not whole 64-byte pieces
+// (CACHED) are read and written through the caches, where neighbouring rows
+// that share a line meet; all others past them (Adagrad, means kept, us past
+// the caches and through them: uniform IDs, D = 20, 3 M positions 515 and 427,
+// D = 4, 300,007 158 and 116, D = 28, 4.3 M 858 and 689; Zipf IDs, D = 28, 1.6 M 211
+// and 219, 4.3 M 459 and 449; 64-byte rows, uniform, D = 16, 1.6 M 247 and 264, D =
+// 48 408 and 475; the means alone, D = 24, 1.6 M 174 and 203).
+template <int LPR, int APPLY, bool CACHED>
 __global__ void __launch_bounds__(kSegBlock) __attribute__((amdgpu_waves_per_eu(4)))
 seg_rows_kernel(SegmentArgs a, const uint32_t* __restrict__ packed, const uint32_t* __restrict__ base, int span,
                 int bshift, SegPartials part, const uint32_t* __restrict__ seg_start,
@@ -764,13 +781,16 @@ seg_rows_kernel(SegmentArgs a, const uint32_t* __restrict__ packed, const uint32
   constexpr int kPart = kBatchPart;
   constexpr bool kPark = APPLY != 0 || LPR <= 16;
   // Rounds of rows in flight: what 128 registers and 40 KB of LDS per block
-  // (four waves per SIMD) allow.  Four rounds leave no LDS for chain sums of
-  // their own (kOwnAcc): those then share the ring, which has to be emptied
-  // once more.  Measured in turn in one process: Adagrad, D = 32, 65.5 M
-  // positions 3399 us with four rounds, 3416 with two and sums of their own; D =
-  // 64, a step of 852 K 249 and 254; where two rounds are the most either way
-  // the sums of their own win (D = 32 with Adam, 6.5 M positions 612 and 618;
-  // D = 16, a step of 20,480 56 and 58).
+  // (four waves per SIMD) allow.  With one or two lanes per row, where a ring
+  // entry is mostly its place, counts and row, the arrays take 51 and 41 KB:
+  // three waves.  Chain sums that share the ring would bring two lanes to four
+  // waves, but are slower (20,480 Zipf positions, D = 8 55 and 58 us).  Four
+  // rounds leave no LDS for chain sums of their own (kOwnAcc): those then share
+  // the ring, which has to be emptied once more.  Measured in turn in one
+  // process: Adagrad, D = 32, 65.5 M positions 3399 us with four rounds, 3416 with
+  // two and sums of their own; D = 64, a step of 852 K 249 and 254; where two rounds
+  // are the most either way the sums of their own win (D = 32 with Adam, 6.5 M
+  // positions 612 and 618; D = 16, a step of 20,480 56 and 58).
   constexpr bool kOwnAcc = !(APPLY == 1 && LPR >= 8);
   constexpr int kR = LPR <= 4 ? 1 : (kOwnAcc ? 2 : 4);
   constexpr int kPop = kR * GW;
@@ -797,6 +817,10 @@ seg_rows_kernel(SegmentArgs a, const uint32_t* __restrict__ packed, const uint32
   __shared__ uint32_t s_cnum[kHotSlots];
   // rounded reciprocals of the small divisors (a segment's contribution count)
   __shared__ double s_recip[kRecipMax + 1];
+  static_assert(LPR < 4 || sizeof(s_park) + sizeof(s_park_out) + sizeof(s_park_cw) + sizeof(s_park_key) +
+                                   sizeof(s_acc) + sizeof(s_cc) + sizeof(s_ww) + sizeof(s_seg) + sizeof(s_flags) +
+                                   sizeof(s_cnum) + sizeof(s_recip) <= 40960,
+                "four blocks per compute unit");
 
   const int64_t N = a.N;                                   // occurrences
   const int64_t n = a.n_dev ? (int64_t)*a.n_dev : a.N;     // sorted positions
@@ -977,16 +1001,16 @@ seg_rows_kernel(SegmentArgs a, const uint32_t* __restrict__ packed, const uint32
           act[r] = outv[r] < N && (s_park_cw[w][slot[r]] >> 16) > 0 && lane_on && (int64_t)k < a.R;
           row[r] = act[r] ? (int64_t)k : 0;
           const int64_t at = act[r] ? row[r] * D + gl * 4 : 0;
-          pv[r] = load_stream(reinterpret_cast<const f32x4*>(a.ap.p + at));
-          sv[r] = load_stream(reinterpret_cast<const f32x4*>(a.ap.s1 + at));
-          if (APPLY == 2) vv[r] = load_stream(reinterpret_cast<const f32x4*>(a.ap.s2 + at));
+          pv[r] = load_row<CACHED>(reinterpret_cast<const f32x4*>(a.ap.p + at));
+          sv[r] = load_row<CACHED>(reinterpret_cast<const f32x4*>(a.ap.s1 + at));
+          if (APPLY == 2) vv[r] = load_row<CACHED>(reinterpret_cast<const f32x4*>(a.ap.s2 + at));
         }
       }
 #pragma unroll
       for (int r = 0; r < kR; ++r) {
         if (outv[r] >= N) continue;
         const f32x4 g = s_park[w][slot[r]][gl];
-        if (lane_on && (!APPLY || a.agg)) store_stream(reinterpret_cast<f32x4*>(a.agg + outv[r] * D + gl * 4), g);
+        if (lane_on && (!APPLY || a.agg)) store_row<CACHED>(reinterpret_cast<f32x4*>(a.agg + outv[r] * D + gl * 4), g);
         if (gl == 0) {
           const uint32_t v = s_park_cw[w][slot[r]];
           a.contrib_count[outv[r]] = (int32_t)(v & 0xffffu);
@@ -997,9 +1021,9 @@ seg_rows_kernel(SegmentArgs a, const uint32_t* __restrict__ packed, const uint32
         if (APPLY && act[r]) {
           const int64_t at = row[r] * D + gl * 4;
           update4(APPLY, a.ap.c, pv[r], sv[r], vv[r], g);
-          store_stream(reinterpret_cast<f32x4*>(a.ap.p + at), pv[r]);
-          store_stream(reinterpret_cast<f32x4*>(a.ap.s1 + at), sv[r]);
-          if (APPLY == 2) store_stream(reinterpret_cast<f32x4*>(a.ap.s2 + at), vv[r]);
+          store_row<CACHED>(reinterpret_cast<f32x4*>(a.ap.p + at), pv[r]);
+          store_row<CACHED>(reinterpret_cast<f32x4*>(a.ap.s1 + at), sv[r]);
+          if (APPLY == 2) store_row<CACHED>(reinterpret_cast<f32x4*>(a.ap.s2 + at), vv[r]);
         }
       }
       first_parked = ring(first_parked + count);
@@ -1532,11 +1556,21 @@ static hipError_t launch_rows(const SegmentArgs& a, const uint32_t* packed, cons
   const int64_t tiles = L.row_tiles;
   const dim3 grid((unsigned)tiles), block(kSegBlock);
   const int span = L.span, bshift = base_shift(span);
-#define GBA_ROWS(AP) \
-  hipLaunchKernelGGL((seg_rows_kernel<LPR, AP>), grid, block, 0, stream, a, packed, base, span, bshift, part, seg_start, cnum)
-  if (a.ap.mode == 1) GBA_ROWS(1);
-  else if (a.ap.mode == 2) GBA_ROWS(2);
-  else GBA_ROWS(0);
+#define GBA_ROWS(AP, CACHED)                                                                                          \
+  hipLaunchKernelGGL((seg_rows_kernel<LPR, AP, CACHED>), grid, block, 0, stream, a, packed, base, span, bshift, part, \
+                     seg_start, cnum)
+  // rows of up to 32 floats that are not whole 64-byte pieces: below 128 bytes
+  constexpr bool kNarrow = LPR <= 8;
+  const bool cached = kNarrow && a.D % 16 != 0;
+  if (a.ap.mode == 1) {
+    if (cached) GBA_ROWS(1, kNarrow);
+    else GBA_ROWS(1, false);
+  } else if (a.ap.mode == 2) {
+    if (cached) GBA_ROWS(2, kNarrow);
+    else GBA_ROWS(2, false);
+  } else {
+    GBA_ROWS(0, false);
+  }
 #undef GBA_ROWS
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

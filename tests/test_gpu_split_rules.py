@@ -80,11 +80,11 @@ def test_segments_over_tile_groups(N, plan):
 
 
 @pytest.mark.parametrize("opt,decay", [("adagrad", "token"), ("adagrad", "id_tag"), ("adam", "id_tag")])
-@pytest.mark.parametrize("D", [4, 12, 128, 256])
+@pytest.mark.parametrize("D", [4, 12, 16, 28, 128, 256])
 def test_fused_apply_at_the_other_widths(D, opt, decay):
     """The row pass applies the rows at every number of lanes per row (one to
-    64 groups per wave share a ring of finished segments): table, state, tags and
-    counts are bitwise those of the aggregation and the row apply as two calls.
+    64 groups per wave share a ring of finished segments; rows that are not
+    whole 64-byte pieces go through the caches): table, state, tags and counts are bitwise those of the aggregation and the row apply as two calls.
     Few long segments and many short ones, so that the ring fills unevenly."""
     K, R = 9, 30_000
     rng = np.random.default_rng(D)
