@@ -37,12 +37,16 @@ def test_row_spans_of_small_inputs(D, N):
     _check_sparse(res, ids, rows, off, w, tokens, 60, 2, expect_exact=True)
 
 
-@pytest.mark.parametrize("n", [1, 1023, 1024, 1025, 4096, 4097, 16_385, 1_048_577,
-                               4096 * 1024 - 1025, 4096 * 1024 + 1, 16 * 1024 * 1024 + 1, 17 * 1024 * 1024 + 1025])
-def test_run_numbers_over_tile_groups(n):
-    """Every position's run number, across tiles, groups of tiles and the size
-    from which the group counts are scanned by a launch of their own."""
-    R, D = 3_000_000, 4
+@pytest.mark.parametrize("n,D", [(n, 4) for n in (1, 1023, 1024, 1025, 4096, 4097, 16_385, (1 << 19) - 1, 1 << 19, 1_048_577,
+                                                 4096 * 1024 - 1025, 4096 * 1024 + 1, 16 * 1024 * 1024 + 1,
+                                                 17 * 1024 * 1024 + 1025, (1 << 25) + 1025)] +
+                         [(257, 32), (3 * 1024 * 1024 - 1, 32), (3 * 1024 * 1024 + 1, 24), (600_001, 12),
+                          (1 << 25, 8)])
+def test_run_numbers_over_tile_groups(n, D):
+    """Every position's run number, across tiles, groups of tiles, the sizes
+    from which a block takes a whole tile, from which the group counts are
+    scanned by a launch of their own and from which the rows are gathered by one."""
+    R = 3_000_000
     g = torch.Generator(device=DEV).manual_seed(n)
     ids = torch.randint(0, R, (n,), device=DEV, generator=g)
     table = torch.arange(R * D, device=DEV, dtype=torch.float32).reshape(R, D)
