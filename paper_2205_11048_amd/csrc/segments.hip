@@ -834,7 +834,6 @@ seg_rows_kernel(SegmentArgs a, const uint32_t* __restrict__ packed, const uint32
   __syncthreads();
   const bool by_k = a.norm == GBA_NORM_BY_K;
   const double recip_k = 1.0 / (double)a.K;
-  const bool small_k = a.K <= kRecipMax;
 
   const int w = threadIdx.x / kWave;
   const int lane = lane_id();
@@ -865,8 +864,8 @@ seg_rows_kernel(SegmentArgs a, const uint32_t* __restrict__ packed, const uint32
     uint32_t cur_key = key0;   // row of the open segment (row apply)
     auto mean_of = [&](f64x4 sum, int count) {
       const double div = by_k ? (double)a.K : (double)count;
-      // a segment has at most K contributions: the table covers every count when K is small
-      const double y = by_k ? recip_k : (small_k ? s_recip[count] : 1.0 / div);
+      // counts are at most K unless the offsets are out of order
+      const double y = by_k ? recip_k : ((uint32_t)count <= (uint32_t)kRecipMax ? s_recip[count] : 1.0 / div);
       return narrow(div_rounded(sum, div, y));
     };
     // A segment of this group is finished (mc: the lanes of the wave's groups

@@ -136,3 +136,23 @@ def test_fractional_weights_at_the_ends_of_the_input(N, R, plan):
     w = np.array([1.0, 0.5, 0.0, 1.0, 0.25, 0.0, 1.0, 0.75], np.float32)
     res = _run_sparse(ids, rows, off, w, tokens, 10, 2, R, plan=plan)
     _check_sparse(res, ids, rows, off, w, tokens, 10, 2, expect_exact=True)
+
+
+@pytest.mark.parametrize("D", [4, 32, 64])
+@pytest.mark.parametrize("opt", ["adagrad", "adam"])
+def test_offsets_out_of_order(opt, D):
+    """Offsets that go up and down are reported; a segment may then change its
+    contribution more often than there are contributions, past the row pass's
+    table of reciprocals."""
+    K, R, N = 200, 1_000, 40_000
+    rng = np.random.default_rng(D)
+    off = rng.integers(0, N + 1, K + 1)
+    off[0], off[K] = 0, N
+    ids = np.where(rng.random(N) < 0.5, 5, rng.integers(0, R, N)).astype(np.int64)
+    rows = np.zeros((N, D), np.float32)
+    tokens = np.full(K, 1000)
+    table0, slots0 = _table_and_state(R, D, opt, 5)
+    out = _sparse_step(dev(ids), dev(rows), dev(off.astype(np.int64)), dev(np.ones(K, np.float32)), dev(tokens), 1000, 3,
+                       R, None, "token", opt, True, True, table0, slots0)
+    assert out["err"] == gba.DERR_OFFSETS
+    assert int(out["num_unique"][0]) == np.unique(ids).size
