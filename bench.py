@@ -183,7 +183,7 @@ def run_workload(name, args, torch, gba_step_mod, sdev, gba):
             ev["s0"].record(stream)
         if not args.separate_sparse:
             # one call: the rows are applied as the aggregation finishes them
-            # (agg kept only where the row width takes the separate apply)
+            # (the means are stored where the size query counts room for them)
             agg = None if st.fuses_rows[w.optimizer] else st.agg
             sparse = (ds.ids, ds.rows, ds.offsets, w.R, st.w, ds.tokens, ds.step, w.iota, ds.tags, decay,
                       gba.NORM_PER_ID_COUNT, st.unique_ids, st.seg_offsets, st.contrib_count, st.active_count, agg,
@@ -387,7 +387,7 @@ def run_workload(name, args, torch, gba_step_mod, sdev, gba):
     end.record(stream)
     torch.cuda.synchronize()
     pull_ms = start.elapsed_time(end) / n_pull
-    # the same request replayed from a captured HIP graph: the 17 small launches
+    # the same request replayed from a captured HIP graph: the small launches
     # of one request then cost no host work
     pg = torch.cuda.CUDAGraph()
     side = torch.cuda.Stream()

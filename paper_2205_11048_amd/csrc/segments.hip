@@ -10,24 +10,26 @@
 // Work is split by sorted position, not by segment, so a Zipf-hot ID with
 // millions of occurrences is spread over many blocks and no floating-point
 // atomics are used.  Two passes over the sorted positions:
-//  * seg_meta: one lane per position (coalesced key and index loads) finds
-//    the contribution of the occurrence through a bucket table in LDS, its
-//    weight, and whether it starts a run of equal IDs or a new contribution
-//    inside one.  It numbers the segments, writes their IDs and starts, and
-//    packs (occurrence index, flags) into one word per position.
-//  * seg_rows: a group of LPR lanes (one 16-byte column slice per lane) walks
-//    128 consecutive positions from their packed words, keeping 8 row gathers
-//    in flight and summing each run in float64.  Runs that cross group
-//    boundaries are joined in LDS; runs that cross tile boundaries leave one
-//    partial per tile end, joined by seg_fixup in a fixed order, so results
-//    are deterministic.
+//  * seg_meta: a lane takes four consecutive positions (16-byte key and index
+//    loads) and finds the contribution of each occurrence through a bucket
+//    table in LDS, its weight, and whether it starts a run of equal IDs or a
+//    new contribution inside one.  It numbers the segments, writes their IDs
+//    and starts, and packs (occurrence index, flags) into one word per position.
+//  * seg_rows: a group of LPR lanes (one 16-byte column slice per lane) walks 8
+//    to 128 consecutive positions (rows_span) from their packed words, keeping
+//    four row gathers in flight and summing each run in float64, and applies
+//    the optimiser to the finished rows where the caller asks for it.  Runs
+//    that cross group boundaries are joined in LDS; runs that cross tile
+//    boundaries leave one partial per tile end, joined by seg_fixup in a fixed
+//    order, so results are deterministic.
 //
 // With the split hot-key plan the sort hands over the cold keys and, apart,
 // the occurrences of each hot ID (a few hundred IDs holding about half of all
 // occurrences under Zipf skew).  The passes above then run over the cold keys
 // only and write each segment at its place among all IDs; each hot ID is one
-// long segment, summed by hot_rows (per 4096-occurrence chunk, no per-position
-// segment logic) and finished by hot_finish, both in a fixed order.
+// long segment, summed by hot_rows (per chunk of some 1000 to 4096
+// occurrences, or more of narrow rows, no per-position segment logic) and
+// finished by hot_finish, both in a fixed order.
 #include <algorithm>
 
 #include "gba_device.hpp"
@@ -43,7 +45,6 @@ constexpr int kRounds = 4;                                   // 16-byte loads pe
 constexpr int64_t kMetaTile = (int64_t)kSegBlock * kRounds;  // 1024 positions: 4 per thread of a block
 static_assert(kMetaTile == kRunTile, "run-head tiles are the per-position tiles");
 constexpr int kGroupSpan = 128;                              // positions per lane group (most; hot_rows)
-constexpr int kBaseSpan = 32;                                // the segment count is kept every 32 positions (or every span)
 constexpr int kBatch = 8;                                    // positions per batch of a group
 // Row gathers in flight per group: a batch's rows are gathered and summed in
 // two parts of four, which leaves the fused row pass 121 VGPRs (4 waves per
@@ -104,9 +105,9 @@ static int hot_span(int64_t N, int lpr) {
   const int span = lpr <= 8 ? 32 : (lpr == 16 ? 64 : 128);
   return N >= kHotWideFrom && lpr >= 8 ? std::min(2 * span, kGroupSpan) : span;
 }
-// The segment count is kept at the start of every group.
+// The segment count is kept at the start of every group, and every 32
+// positions of larger ones.
 static int base_shift(int span) { return span >= 32 ? 5 : (span == 16 ? 4 : 3); }
-static_assert(kBaseSpan == 1 << 5, "base_shift");
 // positions per row-pass tile: 4 waves x (64 / LPR) groups x span positions
 static int64_t rows_tile(int lpr, int span) { return (int64_t)kSegWaves * (kWave / lpr) * span; }
 
@@ -1259,8 +1260,8 @@ seg_fixup_kernel(SegmentArgs a, SegPartials part) {
 }
 
 // ------------------------------------------------------------ hot IDs (split plan)
-// Each hot ID's occurrences are one segment, split into chunks of kGroupSpan
-// occurrences per lane group, TILE per block.  The chunk prefix of the runs is
+// Each hot ID's occurrences are one segment, split into chunks of `span`
+// occurrences per lane group (hot_span), TILE per block.  The chunk prefix of the runs is
 // rebuilt by every block from the hot occurrence counts.
 struct HotPartials {
   double* acc;     // [chunks][D] float64 sums of the weighted rows

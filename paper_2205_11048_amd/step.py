@@ -61,7 +61,9 @@ class GBAStep:
         """One push-step.  On the fused dense path, ``keep_g_bar`` also stores
         the dense sum in ``self.g_bar`` (the separate path always does); on the
         fused sparse path, ``keep_agg`` stores the per-ID means in ``self.agg``
-        (the separate path always does)."""
+        (the separate path always does, and so does the fused one with Adam and
+        for rows not of 20 to 32 floats: without ``agg`` the call would ask for
+        a larger workspace)."""
         if optimizer not in ("adagrad", "adam"):
             raise ValueError(optimizer)
         gba_token_weights(tokens, step, iota, self.w, self.staleness, self.num_excluded, self.err,

@@ -126,7 +126,7 @@ def test_fused_sparse_host_checks():
         gba.gba_aggregate_apply_sparse_workspace_size(10, 0, 32, 100, "adagrad")
     with pytest.raises(gba.GBAError):
         gba.gba_aggregate_apply_sparse_workspace_size(10, 3, 32, 100, 3)
-    # the rows are applied in the row pass for Adagrad at 20-32 floats; else the means need room
+    # the size counts room for the means but for Adagrad at 20-32 floats (no longer used)
     n = 100_000
     plain = gba.gba_aggregate_sparse_workspace_size(n, 3, 32, 1000)
     assert gba.gba_aggregate_apply_sparse_workspace_size(n, 3, 32, 1000, "adagrad") == plain

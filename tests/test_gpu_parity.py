@@ -527,8 +527,8 @@ def test_apply_rows_out_of_range_is_reported():
 @pytest.mark.parametrize("opt", ["adagrad", "adam"])
 def test_full_step_small(decay, opt, D, fused):
     """The whole step against the oracle, with the dense and the sparse calls
-    each fused or separate; D = 32 takes the row pass that applies the rows
-    itself, D = 16 the aggregation followed by the row apply."""
+    each fused or separate (the row pass applies the rows itself; the step
+    stores the means too but for Adagrad at D = 32)."""
     fused_dense, fused_sparse = fused
     c = BY_NAME["c0"].scaled(optimizer=opt, lr=0.01 if opt == "adagrad" else 1e-3, D=D)
     hs = workload.host_step(c)
@@ -695,9 +695,8 @@ def _table_and_state(R, D, opt, seed):
 @pytest.mark.parametrize("opt", ["adagrad", "adam"])
 def test_fused_sparse_matches_separate_calls(opt, decay, D, keep_agg):
     """gba_aggregate_apply_sparse_* gives bitwise the table, state and outputs
-    of gba_aggregate_sparse followed by the row apply: with Adagrad, D = 20 and
-    32 update the rows in the row pass, 8 and 64 aggregate and then apply (as
-    Adam does at every width)."""
+    of gba_aggregate_sparse followed by the row apply, with the means stored
+    and without, for one to sixteen lanes per row."""
     K = 12
     sizes = np.random.default_rng(D).integers(0, 12_000, K)
     R = 40_000
@@ -768,7 +767,7 @@ def test_fused_sparse_large_hot_plan(opt, decay):
     table0, slots0 = _table_and_state(R, D, opt, 6)
     plain = gba.gba_aggregate_sparse_plan_workspace_size(N, K, D, R, gba.SORT_HOT)
     fused = gba.gba_aggregate_apply_sparse_workspace_size(N, K, D, R, opt)
-    assert fused == (plain if opt == "adagrad" else plain + N * D * 4)   # Adam's means go through memory
+    assert fused == (plain if opt == "adagrad" else plain + N * D * 4)   # room once used for Adam's means
     tag = workload.tag_values(77, np.arange(R), step) if decay == "id_tag" else None
     d_in = (dev(ids), d_rows, dev(off), dev(w), dev(tokens))
     sep = _sparse_step(*d_in, step, iota, R, tag, decay, opt, False, True, table0, slots0)
