@@ -753,8 +753,8 @@ seg_meta_kernel(SegmentArgs a, RunHeads heads, const int32_t* __restrict__ bucke
 // 100).  The segments a group closes after its last position go through the
 // ring too, so the wave's last updates share two or three memory latencies
 // instead of taking two each (20,480 positions at D = 16: 20 -> 17.5 us; 6.5 M
-// at D = 32 with Adam 299 -> 291).  Bound: random row accesses, some 35-39 G 128-byte lines a second
-// read and written at every width (a read-only gather reaches 47-50); D = 32
+// at D = 32 with Adam 299 -> 291).  Bound: random row accesses, some 34-36 G 128-byte lines a second
+// read and written at 16, 32 and 64 floats (a read-only gather reaches 47-50); D = 32
 // with Adam, 6.5 M positions, per-ID decay: 303 us for this pass against 144 +
 // 183 + 22 for the pass, the row apply and the tags as launches of their own;
 // D = 16 with Adam 219 against 104 + 119, D = 64 with Adagrad 137 against 63 +
