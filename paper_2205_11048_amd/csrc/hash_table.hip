@@ -90,7 +90,9 @@ hash_clear_kernel(int64_t* __restrict__ slot_ids, int32_t* __restrict__ slot_row
 // for among the first kLeaderRounds distinct values (past them a lane is its
 // own leader).  A frequent ID is nearly always among those.  *repeats, the same
 // in every lane, tells whether one of them was held twice.
-constexpr int kLeaderRounds = 16;
+// With 16 values 300,000 Zipf IDs (exponent 1.05) on an empty index take 97 us,
+// with 22 74 and with 28 67; 450,000 distinct ones 88, 92 and 97.
+constexpr int kLeaderRounds = 22;
 __device__ __forceinline__ int wave_leader(int64_t v, bool* repeats) {
   int lead = lane_id();
   *repeats = false;
