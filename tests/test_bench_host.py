@@ -60,3 +60,12 @@ def test_traffic_is_reported_only_for_the_source_it_was_measured_on(monkeypatch)
     assert bench.measured_traffic(key, "c2") is None          # never measured there
     monkeypatch.setattr(bench, "kernel_source_sha", lambda path: "0" * 16)
     assert bench.measured_traffic(key, "c4") is None          # the kernel changed since
+
+
+def test_traffic_is_found_without_the_launch_rules_choice():
+    """The benchmark names the dense kernel without its vectors per thread."""
+    t = bench.measured_traffic("aggregate_dense_kernel<1, false, 16>", "c4")
+    assert bench.measured_traffic("aggregate_dense_kernel<1, false>", "c4") == t
+    assert bench.measured_traffic("aggregate_dense_kernel<1>", "c4") == t
+    assert bench.measured_traffic("aggregate_dense_kernel<0, false>", "c4") is None
+    assert bench.measured_traffic("aggregate_dense_kernel<2, false>", "c4") is None
